@@ -499,6 +499,14 @@ struct GraphKey {
   }
 };
 
+// Partial images of the stage-wise accumulate call, one per stream.
+struct StageWorkspace {
+  hipStream_t stream = nullptr;
+  void* mem = nullptr;
+  size_t bytes = 0;
+};
+constexpr int kStageStreams = 4;
+
 struct epic_plan_s {
   int device = 0;
   int n_cu = 256;
@@ -506,6 +514,7 @@ struct epic_plan_s {
   // scratch
   void* d_scratch = nullptr;
   size_t scratch_bytes = 0;
+  StageWorkspace stage_ws[kStageStreams];
   uint64_t generation = 1;   // bumped whenever device tables or scratch move
   // options
   int splits = 0;
@@ -580,6 +589,38 @@ int plan_scratch(epic_plan_t p, size_t bytes, void** out) {
   }
   *out = p->d_scratch;
   return EPIC_OK;
+}
+
+// Workspace of the stage-wise accumulate call on stream `s` (its partial
+// images), or null: the call then runs without one, one workgroup per
+// channel.  Each stream has its own, so calls on several streams stay
+// independent: the first kStageStreams streams of a plan, kept until the plan
+// goes.  A captured call gets none, since its replays may run on any stream.
+float* stage_workspace(epic_plan_t p, hipStream_t s, size_t bytes) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  for (StageWorkspace& w : p->stage_ws) {
+    if (w.mem && w.stream != s) continue;
+    if (bytes > w.bytes) {
+      if (w.mem) {
+        if (hipStreamSynchronize(s) != hipSuccess) return nullptr;   // an earlier call may still use it
+        hipFree(w.mem);
+        w = StageWorkspace{};
+      }
+      if (hipMalloc(&w.mem, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        w = StageWorkspace{};
+        return nullptr;
+      }
+      w.stream = s;
+      w.bytes = bytes;
+    }
+    return static_cast<float*>(w.mem);
+  }
+  return nullptr;
 }
 
 int check_plan(epic_plan_t p, int array) {
@@ -911,6 +952,7 @@ int epic_plan_destroy(epic_plan_t plan) {
   hipDeviceSynchronize();
   for (auto& ap : plan->arrays) free_array(ap);
   hipFree(plan->d_scratch);
+  for (auto& w : plan->stage_ws) hipFree(w.mem);
   for (auto& t : plan->timers) {
     hipEventDestroy(t.a);
     hipEventDestroy(t.b);
@@ -1152,7 +1194,8 @@ int epic_grid(epic_plan_t plan, int32_t array, const void* efield, int64_t t0, i
   if (nt > 0 && (!efield || !u || !grid)) return fail(EPIC_ERR_ARG, "efield, u and grid must not be NULL");
   if ((rc = check_aligned({{efield, "efield"}, {u, "u"}, {grid, "grid"}}))) return rc;
   epic::GridArgs a{static_cast<const uint8_t*>(efield), t0, nt, ap.h.F, ap.h.na, ap.h.efmt,
-                   reinterpret_cast<const float2*>(u), ap.d_slots, ap.n_slots, reinterpret_cast<float2*>(grid)};
+                   reinterpret_cast<const float2*>(u), ap.d_slots, ap.n_slots, reinterpret_cast<float2*>(grid),
+                   plan->n_cu, ap.d_slots_h, ap.n_slots_h0, ap.n_slots_h1};
   hipError_t e = epic::launch_grid(ap.h.nx, a, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? EPIC_OK : hip_fail(e, "epic_grid launch");
 }
@@ -1168,9 +1211,14 @@ int epic_image_accumulate(epic_plan_t plan, int32_t array, const float* grid, in
   if (tap && !ap.has_model) return fail(EPIC_ERR_STATE, "tap requested but no model (calibrator pixel) set");
   if ((rc = check_aligned({{grid, "grid"}, {image, "image"}, {tap, "tap"}}))) return rc;
   if (ap.h.na_eff < 1) return fail(EPIC_ERR_ARG, "all antennas are flagged");
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  int splits = epic::image_acc_splits(ap.h.nx, ap.h.F, nt, plan->n_cu);
+  const size_t need = size_t(splits) * ap.h.F * ap.h.nx * ap.h.ny * sizeof(float);
+  float* partial = splits > 1 ? stage_workspace(plan, s, need) : nullptr;
+  if (!partial) splits = 1;
   epic::ImageAccArgs a{reinterpret_cast<const float2*>(grid), nt, ap.h.F, float(1.0 / ap.h.na_eff), image,
-                       reinterpret_cast<float2*>(tap), tap ? ap.d_k0 : nullptr};
-  hipError_t e = epic::launch_image_acc(ap.h.nx, a, static_cast<hipStream_t>(stream));
+                       reinterpret_cast<float2*>(tap), tap ? ap.d_k0 : nullptr, splits, partial};
+  hipError_t e = epic::launch_image_acc(ap.h.nx, a, s);
   return e == hipSuccess ? EPIC_OK : hip_fail(e, "epic_image_accumulate launch");
 }
 

@@ -64,6 +64,10 @@ struct GridArgs {
   const uint2* slots;
   int n_slots;
   float2* grid;             // [nt][F][N][N]
+  int n_cu;
+  // half-frame schedules of the 64 x 64 grid, as in ImageArgs
+  const uint2* slots_h = nullptr;
+  int n_slots_h0 = 0, n_slots_h1 = 0;
 };
 
 // Stage-wise transform + accumulate from HBM grids.
@@ -74,7 +78,11 @@ struct ImageAccArgs {
   float* image;             // [F][N][N] +=
   float2* tap;              // [nt][F] or null
   const int* k0;            // [F][2] (kx, ky)
+  int splits;               // workgroups per channel
+  float* partial;           // [splits][F][N*N] when splits > 1
 };
+// Partial images of one accumulate call at most (its workspace: 16 MiB at 64 x 64).
+constexpr int kAccMaxPartials = 1024;
 
 // EPICal solve over all intervals (fast path).
 struct SolveArgs {
@@ -259,6 +267,8 @@ hipError_t launch_grid(int N, const GridArgs& a, hipStream_t s);
 // n integer-format samples (ci4 / ci8) decoded as the imaging engines decode
 // them, to int16 (re, im) pairs
 hipError_t launch_unpack(const uint8_t* efield, int64_t n, int fmt, int16_t* out, hipStream_t s);
+// time splits per channel of launch_image_acc when it has a workspace
+int image_acc_splits(int N, int F, int nt, int n_cu);
 hipError_t launch_image_acc(int N, const ImageAccArgs& a, hipStream_t s);
 hipError_t launch_reduce(const float* partial, int splits, int64_t per_split, double scale,
                          float* image, hipStream_t s);

