@@ -80,24 +80,34 @@ __device__ __forceinline__ void run_item(const ImageArgs& a, int code, int4 w, u
     case fft8_code(32, 4): fft8_call<32, 4>(a, w, smem); break;
     case pair_code(2, kCI8): pair_call<2, kCI8>(a, w, smem); break;
     case pair_code(2, kCI4): pair_call<2, kCI4>(a, w, smem); break;
+    case pair_code(2, kCF32): pair_call<2, kCF32>(a, w, smem); break;
     case pair_code(4, kCI8): pair_call<4, kCI8>(a, w, smem); break;
     case pair_code(4, kCI4): pair_call<4, kCI4>(a, w, smem); break;
+    case pair_code(4, kCF32): pair_call<4, kCF32>(a, w, smem); break;
     case cls_pair_code(2, kCI8, false): cls_pair_call<2, kCI8, false>(a, w, smem); break;
     case cls_pair_code(2, kCI4, false): cls_pair_call<2, kCI4, false>(a, w, smem); break;
+    case cls_pair_code(2, kCF32, false): cls_pair_call<2, kCF32, false>(a, w, smem); break;
     case cls_pair_code(2, kCI8, true): cls_pair_call<2, kCI8, true>(a, w, smem); break;
     case cls_pair_code(2, kCI4, true): cls_pair_call<2, kCI4, true>(a, w, smem); break;
+    case cls_pair_code(2, kCF32, true): cls_pair_call<2, kCF32, true>(a, w, smem); break;
     case cls_pair_code(4, kCI8, false): cls_pair_call<4, kCI8, false>(a, w, smem); break;
     case cls_pair_code(4, kCI4, false): cls_pair_call<4, kCI4, false>(a, w, smem); break;
+    case cls_pair_code(4, kCF32, false): cls_pair_call<4, kCF32, false>(a, w, smem); break;
     case cls_pair_code(4, kCI8, true): cls_pair_call<4, kCI8, true>(a, w, smem); break;
     case cls_pair_code(4, kCI4, true): cls_pair_call<4, kCI4, true>(a, w, smem); break;
+    case cls_pair_code(4, kCF32, true): cls_pair_call<4, kCF32, true>(a, w, smem); break;
     case dense_code(2, kCI8, 2): dense_call<2, kCI8, 2>(a, w, smem); break;
     case dense_code(2, kCI4, 2): dense_call<2, kCI4, 2>(a, w, smem); break;
+    case dense_code(2, kCF32, 2): dense_call<2, kCF32, 2>(a, w, smem); break;
     case dense_code(4, kCI8, 2): dense_call<4, kCI8, 2>(a, w, smem); break;
     case dense_code(4, kCI4, 2): dense_call<4, kCI4, 2>(a, w, smem); break;
+    case dense_code(4, kCF32, 2): dense_call<4, kCF32, 2>(a, w, smem); break;
     case dense_code(2, kCI8, 4): dense_call<2, kCI8, 4>(a, w, smem); break;
     case dense_code(2, kCI4, 4): dense_call<2, kCI4, 4>(a, w, smem); break;
+    case dense_code(2, kCF32, 4): dense_call<2, kCF32, 4>(a, w, smem); break;
     case dense_code(4, kCI8, 4): dense_call<4, kCI8, 4>(a, w, smem); break;
     case dense_code(4, kCI4, 4): dense_call<4, kCI4, 4>(a, w, smem); break;
+    case dense_code(4, kCF32, 4): dense_call<4, kCF32, 4>(a, w, smem); break;
     default: break;
   }
 }

@@ -51,6 +51,56 @@ __device__ __forceinline__ void gstore(T* p, T v) {
   }
 }
 
+// The same from a byte offset of up to 32 bits beyond `base`: with a
+// wave-uniform base the access takes the scalar base and the lane's offset as
+// they are, without a 64-bit address per lane.
+template <typename T>
+__device__ __forceinline__ T gload_at(const void* base, uint32_t off) {
+  const __attribute__((address_space(1))) char* p = (const __attribute__((address_space(1))) char*)base + off;
+  if constexpr (sizeof(T) == 8 && alignof(T) >= 8) {
+    const gvec2 v = *(const __attribute__((address_space(1))) gvec2*)p;
+    T r;
+    __builtin_memcpy(&r, &v, 8);
+    return r;
+  } else {
+    return *(const __attribute__((address_space(1))) T*)p;
+  }
+}
+
+// Complex value at an LDS address `off` bytes past `base`.
+__device__ __forceinline__ float2& lds_at(float2* base, uint32_t off) {
+  return *reinterpret_cast<float2*>(reinterpret_cast<char*>(base) + off);
+}
+__device__ __forceinline__ float2 lds_at(const float2* base, uint32_t off) {
+  return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base) + off);
+}
+
+// An opaque copy of a lane value: addresses computed from it are not hoisted
+// out of the frame loop, where they would hold registers that the FFTs need.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// The wave's index in its workgroup as a scalar: what is computed from it (the
+// wave's samples, their rows and intervals) then stays in the scalar unit.
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6); }
+
+// Calibration interval of ascending samples t: divided out only when t passes
+// the end of the last one (a 64-bit division per frame was 4% of the vector
+// instructions of the 64 x 64 engine).
+struct IntervalCursor {
+  int64_t t_cal, n = 0, end = -1;
+  __device__ __forceinline__ explicit IntervalCursor(int64_t t_cal_) : t_cal(t_cal_) {}
+  __device__ __forceinline__ int64_t at(int64_t t) {
+    if (t >= end) {
+      n = t / t_cal;
+      end = n == 0 ? t_cal : (n + 1) * t_cal;
+    }
+    return n;
+  }
+};
+
 // A raw packed sample held in registers until it is used (so that a prefetch
 // does not force the wait for the load at the point of issue).
 struct Raw {
@@ -79,13 +129,13 @@ __device__ __forceinline__ Raw load_raw(const uint8_t* row, int a, int fmt) {
 __device__ __forceinline__ Raw load_raw_global(const uint8_t* row, int a, int fmt) {
   Raw r;
   if (fmt == kCI4) {
-    r.x = gload(row + a);
+    r.x = gload_at<uint8_t>(row, uint32_t(a));
     r.y = 0;
   } else if (fmt == kCI8) {
-    r.x = gload(reinterpret_cast<const uint16_t*>(row) + a);
+    r.x = gload_at<uint16_t>(row, 2u * uint32_t(a));
     r.y = 0;
   } else {
-    const uint2 v = gload(reinterpret_cast<const uint2*>(row) + a);
+    const uint2 v = gload_at<uint2>(row, 8u * uint32_t(a));
     r.x = v.x;
     r.y = v.y;
   }
@@ -136,7 +186,10 @@ struct Geo {
 // w * E'_a (E'_a staged in LDS by the antenna lanes) and stores the cell with
 // a plain LDS write -- no atomics.  The host builds the schedule, balanced
 // over lanes: per lane a list of slots (lane fastest in memory), each
-//   code = antenna | cell offset << 12 | first-of-cell << 31,  weight (float)
+//   8 * antenna | 8 * cell offset << 16,  weight (float; sign bit: first of its cell)
+// The halves of the first word are LDS byte offsets as they stand (added to
+// the staging and frame addresses in one instruction each) and weights are
+// never negative, so that a slot takes seven vector instructions.
 // A lane's slots of one cell are consecutive; every slot stores the running
 // sum, so the cell's last slot leaves the full sum.  Padding slots have zero
 // weight and store into a pad column that the transform never reads.  Cells
@@ -207,14 +260,17 @@ __device__ __forceinline__ void grid_frame(float2* buf, const float2* epr, const
       const int s = s0 + k < S ? s0 + k : S - 1;
       e[k] = col[s * L];
     });
-    static_for<0, B>([&](auto kc) { ev[decltype(kc)::value] = epr[e[decltype(kc)::value].x & kSlotAntMask]; });
     static_for<0, B>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
-      const float w = __uint_as_float(e[k].y);
-      const bool first = int(e[k].x) < 0;
+      ev[k] = lds_at(epr, e[k].x & 0xffffu);
+    });
+    static_for<0, B>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      const float w = fabsf(__uint_as_float(e[k].y));
+      const bool first = int(e[k].y) < 0;
       acc.x = fmaf(w, ev[k].x, first ? 0.f : acc.x);
       acc.y = fmaf(w, ev[k].y, first ? 0.f : acc.y);
-      if (s0 + k < S) buf[(e[k].x >> kSlotCellShift) & kSlotCellMask] = acc;
+      if (s0 + k < S) lds_at(buf, e[k].x >> 16) = acc;
     });
   }
 }
@@ -391,6 +447,14 @@ inline int tab_slots_for(int N, int apl) {
     case 64 * 16 + 8: return Budget<64, 8>::TAB_SLOTS;
     default: return 0;
   }
+}
+
+// f(integral_constant<int, FMT>) for the E-field format `fmt`.
+template <typename F>
+inline void with_format(int fmt, F&& f) {
+  if (fmt == kCI4) f(std::integral_constant<int, kCI4>{});
+  else if (fmt == kCI8) f(std::integral_constant<int, kCI8>{});
+  else f(std::integral_constant<int, kCF32>{});
 }
 
 template <int N, template <int, int> class Launch, typename Args>

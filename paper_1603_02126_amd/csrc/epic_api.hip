@@ -222,7 +222,8 @@ void model_tables(const HostArray& h, const epic_model_desc* m, ModelTables& t, 
 // Owner-computes gridding schedule of the N <= 64 imaging engine: every
 // nonzero cell goes to one lane (greedy balance of contribution counts); each
 // lane gets consecutive slots per owned cell, coded
-//   antenna | LDS cell offset << 12 | first-of-cell << 31,  weight bits.
+//   8 * antenna | 8 * LDS cell offset << 16,  weight (sign bit: first of its cell)
+// (transposed, the DFT-GEMM engine's: antenna | offset << 12 | first << 31, weight).
 // Padding slots store zero into the pad column (offset = grid size).
 // Returns the slot count S; table is [S][L] (lane fastest), 2 words each.
 // half >= 0: the columns 32 half <= x < 32 half + 32 only, at offsets
@@ -257,7 +258,18 @@ int build_slots(const HostArray& h, int L, int pitch, std::vector<uint32_t>& tab
   }
   size_t S = 0;
   for (int l = 0; l < L; ++l) S = std::max(S, load[l]);
-  const uint32_t pad = uint32_t(half >= 0 ? 32 : h.nx) << 12;   // row 0, first pad column
+  const uint32_t pad = uint32_t(half >= 0 ? 32 : h.nx);   // row 0, first pad column
+  auto put = [&](size_t at, uint32_t ant, uint32_t off, float wf, bool first) {
+    uint32_t wb;
+    std::memcpy(&wb, &wf, 4);
+    if (transposed) {
+      table[at] = ant | off << 12 | uint32_t(first) << 31;
+      table[at + 1] = wb;
+    } else {
+      table[at] = 8 * ant | 8 * off << 16;
+      table[at + 1] = wb | uint32_t(first) << 31;
+    }
+  };
   table.assign(2 * S * L, 0u);
   for (int l = 0; l < L; ++l) {
     size_t s = 0;
@@ -268,29 +280,20 @@ int build_slots(const HostArray& h, int L, int pitch, std::vector<uint32_t>& tab
                                         : uint32_t(cy * pitch + cx);
       const auto& lst = cell[c];
       for (size_t i = 0; i < lst.size(); ++i, ++s) {
-        uint32_t code = uint32_t(lst[i].first) | (off << 12);
-        if (i == 0) code |= 1u << 31;
-        float wf = lst[i].second;
-        uint32_t wb;
-        std::memcpy(&wb, &wf, 4);
-        table[2 * (s * L + l)] = code;
-        table[2 * (s * L + l) + 1] = wb;
+        put(2 * (s * L + l), uint32_t(lst[i].first), off, lst[i].second, i == 0);
       }
     }
-    for (; s < S; ++s) {
-      table[2 * (s * L + l)] = pad | (1u << 31);
-      table[2 * (s * L + l) + 1] = 0u;
-    }
+    for (; s < S; ++s) put(2 * (s * L + l), 0u, pad, 0.f, true);
   }
   return int(S);
 }
 
-// Gridding schedule of the residue-class engine (N = 64 R): contributions are
+// Gridding schedule of the residue-class engines (N = 64 R): contributions are
 // grouped by sub-cell q = j mod 64 and sub-cells are balanced over 64 lanes;
 // each slot keeps the full cell j = 64 p + q so that the kernel can apply the
-// class phase exp(+2 pi i j.c / N).
-// half >= 0: the sub-cell columns 32 half <= qx < 32 half + 32 only (the
-// codes keep the full qx).
+// class phase exp(+2 pi i j.c / N) (epic::cls_slot).
+// half >= 0: the sub-cell columns 32 half <= qx < 32 half + 32 only, with
+// columns re-based to the half (padding slots: weight 0 in its pad column).
 int build_slots_cls(const HostArray& h, std::vector<uint32_t>& table, int half = -1) {
   std::vector<int32_t> ix, iy;
   std::vector<double> w;
@@ -328,18 +331,16 @@ int build_slots_cls(const HostArray& h, std::vector<uint32_t>& table, int half =
       const auto& lst = sub[c];
       for (size_t i = 0; i < lst.size(); ++i, ++s) {
         const Contrib& q = lst[i];
-        uint32_t code = uint32_t(q.a) | uint32_t(q.jx % 64) << 12 | uint32_t(q.jy % 64) << 18 |
-                        uint32_t(q.jx / 64) << 24 | uint32_t(q.jy / 64) << 26 | (1u << 30);
-        if (i == 0) code |= 1u << 31;
+        const uint32_t jx = uint32_t(half >= 0 ? q.jx - 32 * half : q.jx);
         uint32_t wb;
         std::memcpy(&wb, &q.w, 4);
-        table[2 * (s * 64 + l)] = code;
-        table[2 * (s * 64 + l) + 1] = wb;
+        table[2 * (s * 64 + l)] = epic::cls_slot(uint32_t(q.a), jx, uint32_t(q.jy), false);
+        table[2 * (s * 64 + l) + 1] = wb | uint32_t(i == 0) << 31;
       }
     }
     for (; s < S; ++s) {
-      table[2 * (s * 64 + l)] = 1u << 31;   // invalid: zero weight, stores into the pad column
-      table[2 * (s * 64 + l) + 1] = 0u;
+      table[2 * (s * 64 + l)] = epic::cls_slot(0u, half >= 0 ? 32u : 0u, 0u, half < 0);
+      table[2 * (s * 64 + l) + 1] = 1u << 31;
     }
   }
   return int(S);
@@ -386,19 +387,15 @@ int build_slots_dense(const HostArray& h, int owners, int half, std::vector<uint
       const auto& lst = sub[c];
       for (size_t i = 0; i < lst.size(); ++i, ++s) {
         const Contrib& q = lst[i];
-        uint32_t code = uint32_t(q.a) | uint32_t(q.jx % 64) << 12 | uint32_t(q.jy % 64) << 18 |
-                        uint32_t(q.jx / 64) << 24 | uint32_t(q.jy / 64) << 26;
-        if (i == 0) code |= 1u << 31;
-        if (i + 1 == lst.size()) code |= 1u << 30;
         uint32_t wb;
         std::memcpy(&wb, &q.w, 4);
-        table[2 * (s * owners + l)] = code;
-        table[2 * (s * owners + l) + 1] = wb;
+        table[2 * (s * owners + l)] = epic::cls_slot(uint32_t(q.a), uint32_t(q.jx), uint32_t(q.jy), i + 1 == lst.size());
+        table[2 * (s * owners + l) + 1] = wb | uint32_t(i == 0) << 31;
       }
     }
     for (; s < S; ++s) {
-      table[2 * (s * owners + l)] = 1u << 31;
-      table[2 * (s * owners + l) + 1] = 0u;
+      table[2 * (s * owners + l)] = 0u;
+      table[2 * (s * owners + l) + 1] = 1u << 31;
     }
   }
   return int(S);
@@ -462,7 +459,8 @@ struct ArrayPlan {
   int n_slots_dft = 0;
   uint2* d_slots_h = nullptr;     // 64 x 64: half-frame schedule (two halves of rows)
   int n_slots_h0 = 0, n_slots_h1 = 0;
-  uint2* d_slots_m = nullptr;     // 128 / 256, integer formats: multi-class schedules (two halves)
+  uint2* d_degrid = nullptr;      // 64 x 64, up to 256 antennas: degridding table (AdjointArgs)
+  uint2* d_slots_m = nullptr;     // 128 / 256: multi-class schedules (two halves)
   int n_slots_m0 = 0, n_slots_m1 = 0;
   uint2* d_slots_c = nullptr;     // 128 / 256: class schedule of the DFT-GEMM engine (128 owners)
   int n_slots_c = 0;
@@ -551,6 +549,7 @@ void free_array(ArrayPlan& p) {
   hipFree(p.d_slots);
   hipFree(p.d_slots_dft);
   hipFree(p.d_slots_h);
+  hipFree(p.d_degrid);
   hipFree(p.d_slots_m);
   hipFree(p.d_slots_c);
   hipFree(p.d_flag);
@@ -913,6 +912,17 @@ int epic_plan_create(const epic_array_desc* arrays, int32_t n_arrays, epic_plan_
         ap.n_slots_h1 = build_slots(ap.h, 64, epic::kHalfPitch, hi, false, 1);
         tab.insert(tab.end(), hi.begin(), hi.end());
         rc = upload(&ap.d_slots_h, reinterpret_cast<const uint2*>(tab.data()), tab.size() / 2);
+        if (!rc && ap.h.na <= 256) {
+          std::vector<uint32_t> dg(2 * 4 * 256, 0u);
+          for (int an = 0; an < ap.h.na; ++an)
+            for (int k = 0; k < 4; ++k) {
+              const uint32_t c = packed[size_t(an) * 4 + k], x = c & 0xffffu, y = c >> 16;
+              const size_t at = 2 * (size_t(4 * (an / 64) + k) * 64 + an % 64);
+              dg[at] = 8 * (y * epic::kHalfPitch + (x & 31)) | (x >> 5) << 16;
+              std::memcpy(&dg[at + 1], &wf[size_t(an) * 4 + k], 4);
+            }
+          rc = upload(&ap.d_degrid, reinterpret_cast<const uint2*>(dg.data()), dg.size() / 2);
+        }
       }
     } else if (!rc && ap.h.nx == ap.h.ny && (ap.h.nx == 128 || ap.h.nx == 256)) {
       std::vector<uint32_t> tab;
@@ -929,7 +939,7 @@ int epic_plan_create(const epic_array_desc* arrays, int32_t n_arrays, epic_plan_
         ap.n_slots_c = build_slots_dense(ap.h, epic::dft_owners(ap.h.nx), -1, tab);
         rc = upload(&ap.d_slots_c, reinterpret_cast<const uint2*>(tab.data()), tab.size() / 2);
       }
-      if (!rc && ap.h.efmt != EPIC_CF32) {
+      if (!rc) {
         std::vector<uint32_t> hi;
         const int owners = 64 * (ap.h.nx == 256 ? 8 : 4);   // the lanes of a frame's waves
         ap.n_slots_m0 = build_slots_dense(ap.h, owners, 0, tab);
@@ -1313,8 +1323,8 @@ static int solve_ps(const HostArray& h) {
 }
 
 // The persistent batched kernel's body for an array (0: the array is imaged
-// by its own launch in the batched sequence: complex float E-fields at 64 x 64
-// and above, the one-wave class engines, the DFT-GEMM form).
+// by its own launch in the batched sequence: the one-wave engines of 64 x 64
+// and 128 x 128, the DFT-GEMM form).
 static int body_of(epic_plan_t plan, const ArrayPlan& ap) {
   ImageArgs ia = engine_probe(ap);
   ia.n_slots = ap.n_slots;
@@ -1663,7 +1673,11 @@ int epic_run(epic_plan_t plan, const void* const* efield, int64_t n_samples, dou
     return fail(EPIC_ERR_UNSUPPORTED, "gains shared over a band run in the per-array form (EPIC_OPT_BATCH 0 or 2)");
   const bool fused = !any_band && all_batchable && fused_eligible(plan);
   const bool batched = !any_band && all_batchable && (plan->batch == 1 || (plan->batch == 0 && na_arr > 1));
-  if (plan->graph && !batched && !fused)
+  // a graph needs the batched form or a fused run; a single array of float
+  // samples at 64 x 64 and above was never captured without EPIC_OPT_BATCH = 1
+  bool graph_fused = fused;
+  for (const ArrayPlan& ap : plan->arrays) graph_fused = graph_fused && !(ap.h.efmt == EPIC_CF32 && ap.h.nx >= 64);
+  if (plan->graph && !batched && !graph_fused)
     return fail(EPIC_ERR_UNSUPPORTED, "graph replay needs the batched form (EPIC_OPT_BATCH and supported engines)");
   void* scr = nullptr;
   rc = plan_scratch(plan, need, &scr);
@@ -1890,7 +1904,7 @@ int epic_image_adjoint(epic_plan_t plan, int32_t array, const void* efield, int6
   if (e != hipSuccess) return hip_fail(e, "reciprocal launch");
   epic::AdjointArgs a{static_cast<const uint8_t*>(efield), n_samples, h.F, h.na, h.efmt, u, dL_dI, ap.d_slots,
                       ap.n_slots, ap.d_cell_ixy, ap.d_cell_w, h.k2, splits, partial,
-                      ap.d_slots_h, ap.n_slots_h0, ap.n_slots_h1};
+                      ap.d_slots_h, ap.n_slots_h0, ap.n_slots_h1, ap.d_degrid};
   {
     Timed tm(plan, EPIC_TIMER_ADJOINT, s);
     e = epic::launch_adjoint(h.nx, a, s);

@@ -49,7 +49,7 @@ struct ImageArgs {
   int dft_prec = 0;
   const uint2* slots_c = nullptr;
   int n_slots_c = 0;
-  // residue-class engine choice at 128 / 256 with integer samples: 0 = the
+  // residue-class engine choice at 128 / 256: 0 = the
   // default (class-pair engine where it applies, else the dense engine with
   // gridding batches of 2); 2 or 4 = the dense engine with that batch
   int grid_batch = 0;
@@ -153,6 +153,10 @@ struct AdjointArgs {
   // half-frame schedules (64 x 64 two-waves-per-SIMD engine), as in ImageArgs
   const uint2* slots_h = nullptr;
   int n_slots_h0 = 0, n_slots_h1 = 0;
+  // degridding table of that engine, up to 256 antennas: entry (4 i + k) * 64 +
+  // lane is kernel cell k of antenna 64 i + lane: byte offset in the half frame
+  // | column half << 16, weight (0 past the last antenna and for flagged ones)
+  const uint2* degrid = nullptr;
 };
 
 // Batched execution over several arrays (one launch per stage).
@@ -227,7 +231,6 @@ int batch_body(const ImageArgs& a, int N, bool dft);
 hipError_t launch_image_batch(const BatchImageArgs& b, int n_workgroups, hipStream_t s);
 hipError_t launch_solve_batch(const BatchSolveArgs& b, int j, int ps, hipStream_t s);
 hipError_t launch_reduce_batch(const BatchReduceArgs& b, hipStream_t s);
-int cls_variant(int na, int n_slots);
 
 // Snapshot windows of at least this many samples are imaged by all eight
 // waves of a paired-engine workgroup together; shorter ones by one wave each.
@@ -239,13 +242,27 @@ constexpr int64_t kSnapGroupWindow = 64;
 // is the pad that the schedule's padding slots write.
 constexpr int kHalfPitch = 33;
 
+// Slot code of the residue-class engines' gridding schedules:
+//   8 * antenna | jx << 14 | jy << 22 | mark << 30,  and the weight (never
+// negative) with its sign bit set on the first contribution of a sub-cell.
+// (jx, jy) is the full cell 64 p + q, so that one field extraction gives what
+// the class phase needs and its low six bits the sub-cell; in half-frame
+// schedules the column is re-based to the half (q from 0 to 31, 32 = pad).
+// mark: dense schedules, the sub-cell's last contribution; whole-frame
+// schedules, a padding slot.
+__host__ __device__ inline uint32_t cls_slot(uint32_t ant, uint32_t jx, uint32_t jy, bool mark) {
+  return 8 * ant | jx << 14 | jy << 22 | uint32_t(mark) << 30;
+}
+constexpr uint32_t kClsAnt8Mask = 0x3fffu;
+__host__ __device__ inline uint32_t cls_slot_x(uint32_t code) { return (code >> 14) & 255u; }
+__host__ __device__ inline uint32_t cls_slot_y(uint32_t code) { return (code >> 22) & 255u; }
+__host__ __device__ inline bool cls_slot_mark(uint32_t code) { return (code >> 30) & 1u; }
+
 // Launchers: return hipSuccess or the launch error.  N = grid size.
 // Gridding schedule geometry of the N <= 64 engine: lanes per frame and LDS
 // row pitch (complex values) that slot offsets refer to.
 int grid_lanes(int N);
 int grid_pitch(int N);
-// Slot rows available to the N = 128, 256 residue-class engine.
-int cls_table_slots();
 bool image_supported(int N, int na, int n_slots);
 bool pair_engine(const ImageArgs& a, int N);   // the 64 x 64 two-waves-per-SIMD engine applies
 bool cls_pair_engine(const ImageArgs& a, int N);   // the 128 / 256 two-waves-per-SIMD class engine applies

@@ -10,56 +10,45 @@
 // class; the four waves of a workgroup image four classes of the same frame
 // from one shared E' staging area, and each class writes its own interleaved
 // subset of the partial image.
-// Slot code: antenna | qx << 12 | qy << 18 | px << 24 | py << 26 | valid << 30
-//            | first << 31.
+// Slot codes: cls_slot.
 //
-// Two variants: the slot table copied to LDS with a double-buffered staging
-// area (Na <= 512, one barrier per frame), and the "big" variant for dense
-// arrays (Na <= 2048) that reads the table from memory (L1/L2 resident, the
-// same rows for the four waves) with a single staging buffer (two barriers
-// per frame).
+// The arrays that neither two-waves-per-SIMD engine below takes (128 x 128
+// with more than 1024 antennas) are imaged by the one-wave engine here: its
+// slot table is read from memory (L1/L2 resident, the same rows for the four
+// waves), its single staging buffer costs two barriers per frame.
 #pragma once
 #include "engine.h"
 #include "xpose.h"
 
 namespace epic {
 
-constexpr int kClsMaxAnt = 512;
-constexpr int kClsGridBatch = 8;   // gridding slots per batch in the one-wave class engines
+constexpr int kClsMaxAnt = 512;      // class-pair engine
 constexpr int kClsMaxAntBig = 2048;
-constexpr int kClsTabSlots =
-    (kLdsBytes - 4 * Geo<64>::FRAME * 8 - 2 * kClsMaxAnt * 8 - 256 * 8) / (64 * 8);
+constexpr int kClsGridBatch = 8;     // gridding slots per batch in the one-wave engine
 
-template <int R, bool BIG>
-struct ClsSmem {
-  static constexpr int FRAMES = 4 * Geo<64>::FRAME * 8;
-  static constexpr int E_OFF = FRAMES;
-  static constexpr int E_BYTES = BIG ? kClsMaxAntBig * 8 : 2 * kClsMaxAnt * 8;
-  static constexpr int TW_OFF = E_OFF + E_BYTES;
-  static constexpr int T_OFF = TW_OFF + 64 * R * 8;
-  static constexpr int BYTES = T_OFF + (BIG ? 0 : kClsTabSlots * 64 * 8);
+template <int R>
+struct ClsBigSmem {
+  static constexpr int E_OFF = 4 * Geo<64>::FRAME * 8;
+  static constexpr int TW_OFF = E_OFF + kClsMaxAntBig * 8;
+  static constexpr int BYTES = TW_OFF + 64 * R * 8;
 };
 
 // One work item: channel f, class group cg (four classes), time split s.
-// GB: gridding slots per batch; 0 grids one slot at a time (the persistent
-// multi-array kernel, where that form measured faster).
-template <int R, bool BIG, int GB = kClsGridBatch>
-__device__ __forceinline__ void image_cls_item(const ImageArgs& a, int f, int cg, int s, uint8_t* smem) {
-  constexpr int N = 64 * R;
-  constexpr int MAXI = BIG ? kClsMaxAntBig / 256 : kClsMaxAnt / 256;   // antennas per thread
+template <int R>
+__device__ __forceinline__ void image_cls_big_item(const ImageArgs& a, int f, int cg, int s, uint8_t* smem) {
+  constexpr int N = 64 * R, GB = kClsGridBatch;
+  constexpr int MAXI = kClsMaxAntBig / 256;   // antennas per thread
   using G = Geo<64>;
-  using L = ClsSmem<R, BIG>;
+  using L = ClsBigSmem<R>;
   constexpr int P = G::PITCH;
   float2* lds = reinterpret_cast<float2*>(smem);
-  float2* epr_base = reinterpret_cast<float2*>(smem + L::E_OFF);
+  float2* epr = reinterpret_cast<float2*>(smem + L::E_OFF);
   float2* tw = reinterpret_cast<float2*>(smem + L::TW_OFF);
-  const uint2* stab = BIG ? a.slots : reinterpret_cast<const uint2*>(smem + L::T_OFF);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = cg * 4 + wave, cx = c % R, cy = c / R;
   const int64_t tb = a.n_t * s / a.splits, te = a.n_t * (s + 1) / a.splits;
   float2* buf = lds + wave * G::FRAME;
 
-  if constexpr (!BIG) load_slot_table(reinterpret_cast<uint2*>(smem + L::T_OFF), a.slots, a.n_slots, 64);
   for (int k = tid; k < N; k += 256) {
     double sn, cs;
     sincospi(2.0 * double(k) / double(N), &sn, &cs);
@@ -90,7 +79,6 @@ __device__ __forceinline__ void image_cls_item(const ImageArgs& a, int f, int cg
   fetch(tb, tb < te);
   __syncthreads();
   for (int64_t t = tb; t < te; ++t) {
-    float2* epr = BIG ? epr_base : epr_base + ((t - tb) & 1) * kClsMaxAnt;
 #pragma unroll
     for (int i = 0; i < MAXI; ++i) {
       const int an = tid + 256 * i;
@@ -98,53 +86,33 @@ __device__ __forceinline__ void image_cls_item(const ImageArgs& a, int f, int cg
     }
     fetch(t + 1, t + 1 < te);
     __syncthreads();
-    // grid class (cx, cy): owned sub-cells, each contribution phased by exp(+2 pi i j.c / N)
+    // grid class (cx, cy): owned sub-cells, each contribution phased by
+    // exp(+2 pi i j.c / N); slots in batches: the batch's table entries are all
+    // requested before the first is used, so one wait covers them
     float2 sum = make_float2(0.f, 0.f);
-    if constexpr (GB > 0) {
-      // slots in batches: the batch's table entries are all requested before the
-      // first is used (from memory for the dense variant), so one wait covers them
-      const int S = a.n_slots;
-      for (int k0 = 0; k0 < S; k0 += GB) {
-        uint2 e[GB];
-        static_for<0, GB>([&](auto jc) {
-          constexpr int j = decltype(jc)::value;
-          const int k = k0 + j < S ? k0 + j : S - 1;
-          e[j] = BIG ? gload(a.slots + k * 64 + lane) : stab[k * 64 + lane];
-        });
-        static_for<0, GB>([&](auto jc) {
-          constexpr int j = decltype(jc)::value;
-          const uint32_t code = e[j].x;
-          const int qx = (code >> 12) & 63, qy = (code >> 18) & 63;
-          const int jx = qx + 64 * int((code >> 24) & 3), jy = qy + 64 * int((code >> 26) & 3);
-          const float2 ph = tw[(jx * cx + jy * cy) & (N - 1)];
-          const float w = __uint_as_float(e[j].y);
-          const float2 ev = cmul(epr[code & kSlotAntMask], make_float2(w * ph.x, w * ph.y));
-          const float keep = int(code) < 0 ? 0.f : 1.f;   // a cell's first contribution restarts the sum
-          sum.x = fmaf(sum.x, keep, ev.x);
-          sum.y = fmaf(sum.y, keep, ev.y);
-          const int off = (code >> 30) & 1 ? qy * P + qx : 64;
-          if (k0 + j < S) buf[off] = sum;
-        });
-      }
-    } else {
-#pragma unroll 4
-      for (int k = 0; k < a.n_slots; ++k) {
-        const uint2 e = BIG ? gload(a.slots + k * 64 + lane) : stab[k * 64 + lane];
-        const uint32_t code = e.x;
-        const int qx = (code >> 12) & 63, qy = (code >> 18) & 63;
-        const int jx = qx + 64 * int((code >> 24) & 3), jy = qy + 64 * int((code >> 26) & 3);
+    const int S = a.n_slots;
+    for (int k0 = 0; k0 < S; k0 += GB) {
+      uint2 e[GB];
+      static_for<0, GB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const int k = k0 + j < S ? k0 + j : S - 1;
+        e[j] = gload(a.slots + k * 64 + lane);
+      });
+      static_for<0, GB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const uint32_t code = e[j].x;
+        const int jx = int(cls_slot_x(code)), jy = int(cls_slot_y(code));
         const float2 ph = tw[(jx * cx + jy * cy) & (N - 1)];
-        const float w = __uint_as_float(e.y);
-        const float2 ev = cmul(epr[code & kSlotAntMask], make_float2(w * ph.x, w * ph.y));
-        const float keep = int(code) < 0 ? 0.f : 1.f;
+        const float w = fabsf(__uint_as_float(e[j].y));
+        const float2 ev = cmul(lds_at(epr, code & kClsAnt8Mask), make_float2(w * ph.x, w * ph.y));
+        const float keep = int(e[j].y) < 0 ? 0.f : 1.f;   // a cell's first contribution restarts the sum
         sum.x = fmaf(sum.x, keep, ev.x);
         sum.y = fmaf(sum.y, keep, ev.y);
-        const int off = (code >> 30) & 1 ? qy * P + qx : 64;
-        buf[off] = sum;
-      }
+        const int off = cls_slot_mark(code) ? 64 : (jy & 63) * P + (jx & 63);
+        if (k0 + j < S) buf[off] = sum;
+      });
     }
-    if constexpr (BIG) __syncthreads();   // the single staging buffer is rewritten next
-    else wave_lds_sync();
+    __syncthreads();   // the single staging buffer is rewritten next
     float2 v[64];
     transform_frame<64, +1>(buf, v, lane);
     add_norms<64>(acc, v);
@@ -159,7 +127,7 @@ __device__ __forceinline__ void image_cls_item(const ImageArgs& a, int f, int cg
 }
 
 // ---------------------------------------------------------------------------
-// Residue-class engine with two waves per SIMD (integer E-fields, Na <= 512).
+// Residue-class engine with two waves per SIMD (Na <= 512).
 //
 // Eight waves: two frames (samples t, t + 1) x four classes of the class
 // group.  Each wave grids its class of its frame through half a 64 x 64 frame
@@ -198,6 +166,7 @@ template <int R, int B>
 __device__ __forceinline__ void grid_cls_half(float2* H, const float2* epr, const float2* tw, const uint2* stab,
                                               int S, int hf, int cx, int cy, int lam) {
   constexpr int N = 64 * R;
+  const uint32_t cx8 = 8u * uint32_t(cx), cy8 = 8u * uint32_t(cy), k8 = 32u * uint32_t(hf) * cx8;
   int lo = lam;                 // opaque copy: no per-slot table address held across the frame loop
   asm volatile("" : "+v"(lo));
   const uint2* col = stab + lo;
@@ -209,25 +178,24 @@ __device__ __forceinline__ void grid_cls_half(float2* H, const float2* epr, cons
       constexpr int k = decltype(kc)::value;
       e[k] = col[(s0 + k < S ? s0 + k : S - 1) * 64];
     });
+    // table index jx cx + jy cy mod N, in bytes (24-bit multiply-adds)
     static_for<0, B>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       const uint32_t code = e[k].x;
-      const int jx = int((code >> 12) & 63) + 64 * int((code >> 24) & 3);
-      const int jy = int((code >> 18) & 63) + 64 * int((code >> 26) & 3);
-      ph[k] = tw[(jx * cx + jy * cy) & (N - 1)];
-      ev[k] = epr[code & kSlotAntMask];
+      const uint32_t idx = __umul24(cls_slot_x(code), cx8) + (__umul24(cls_slot_y(code), cy8) + k8);
+      ph[k] = lds_at(tw, idx & (8u * N - 8u));
+      ev[k] = lds_at(epr, code & kClsAnt8Mask);
     });
     static_for<0, B>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       const uint32_t code = e[k].x;
-      const float w = __uint_as_float(e[k].y);
-      const float2 c = cmul(ev[k], make_float2(w * ph[k].x, w * ph[k].y));
-      const float keep = int(code) < 0 ? 0.f : 1.f;   // a cell's first contribution restarts the sum
-      sum.x = fmaf(sum.x, keep, c.x);
-      sum.y = fmaf(sum.y, keep, c.y);
-      const int qx = (code >> 12) & 63, qy = (code >> 18) & 63;
-      const int off = (code >> 30) & 1 ? qy * kHalfPitch + qx - 32 * hf : 32;
-      if (s0 + k < S) H[off] = sum;
+      const float w = fabsf(__uint_as_float(e[k].y));
+      const bool first = int(e[k].y) < 0;   // a sub-cell's first contribution restarts the sum
+      const float2 z = make_float2(w * ph[k].x, w * ph[k].y);
+      sum.x = fmaf(ev[k].x, z.x, fmaf(-ev[k].y, z.y, first ? 0.f : sum.x));
+      sum.y = fmaf(ev[k].x, z.y, fmaf(ev[k].y, z.x, first ? 0.f : sum.y));
+      const uint32_t off = __umul24((code >> 22) & 63u, 8u * kHalfPitch) + 8u * ((code >> 14) & 63u);
+      if (s0 + k < S) lds_at(H, off) = sum;
     });
   }
 }
@@ -246,21 +214,19 @@ __device__ __forceinline__ void grid_cls_half_fit(float2* H, const float2* epr, 
 
 template <int R, int FMT, bool DB>
 __device__ __forceinline__ void image_cls_pair_item(const ImageArgs& a, int f, int cg, int s, uint8_t* smem) {
-  static_assert(FMT == kCI4 || FMT == kCI8, "integer E-field formats");
   constexpr int N = 64 * R, NF = 64;
   using L = ClsPairSmem<R, DB>;
   float2* lds = reinterpret_cast<float2*>(smem);
-  const int tid = threadIdx.x, lam = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lam = tid & 63, wave = wave_index();
   const int fs = wave >> 2, ci = wave & 3;          // frame slot, class within the group
   const int c = cg * 4 + ci, cx = c % R, cy = c / R;
-  const int gt = tid & 255;                         // thread within the frame's four waves
   float2* H = lds + wave * L::HALF;
   float2* const e_base = reinterpret_cast<float2*>(smem + L::E_OFF);
   float2* tw = reinterpret_cast<float2*>(smem + L::TW_OFF);
   uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
   const int S0 = a.n_slots_h0, S1 = a.n_slots_h1;
   const int64_t tb = a.n_t * s / a.splits, te = a.n_t * (s + 1) / a.splits;
-  constexpr int bpe = FMT == kCI4 ? 1 : 2;
+  constexpr int bpe = FMT == kCF32 ? 8 : FMT == kCI8 ? 2 : 1;
   constexpr int APT = kClsMaxAnt / 256;             // antennas per staging thread
 
   load_slot_table(stab, a.slots_h, S0 + S1, 64);
@@ -274,32 +240,37 @@ __device__ __forceinline__ void image_cls_pair_item(const ImageArgs& a, int f, i
   float acc[NF];
   static_for<0, NF>([&](auto yc) { acc[decltype(yc)::value] = 0.f; });
   float2 v[NF];
-  uint32_t raw[APT];
+  Raw raw[APT];
+  // antennas lam + 64 ci + 256 i of the frame slot's four waves; a wave whose
+  // first antenna is past the last has none, and lanes past the last repeat it
+  // into staging entries that no slot refers to
+  auto has = [&](int i) { return 256 * i + 64 * ci < a.Na; };
+  auto ant = [&](int i) { return min(lam + 64 * ci + 256 * i, a.Na - 1); };
   auto fetch_raw = [&](int64_t t) {
-    const uint8_t* row = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
+    const uint8_t* row = a.efield + ((t < te ? t : tb) * a.F + f) * int64_t(a.Na) * bpe;
     static_for<0, APT>([&](auto ic) {
-      const int an = gt + 256 * decltype(ic)::value;
-      raw[decltype(ic)::value] = (t < te && an < a.Na) ? load_raw_global(row, an, FMT).x : 0u;
+      constexpr int i = decltype(ic)::value;
+      if (has(i)) raw[i] = load_raw_global(row, ant(i), FMT);
     });
   };
+  static_for<0, APT>([&](auto ic) { raw[decltype(ic)::value] = Raw{0u, 0u}; });
   const int64_t iters = (te - tb + 1) / 2;
+  IntervalCursor interval(a.t_cal);
   fetch_raw(tb + fs);
   for (int64_t it = 0; it < iters; ++it) {
     const int64_t t = tb + 2 * it + fs;
     float2* epr = e_base + ((DB ? int(it & 1) * 2 : 0) + fs) * L::MAXA;
     __builtin_amdgcn_s_setprio(1);   // LDS-bound phases at raised priority (see the 64 x 64 paired engine)
-    // stage E' of this frame (its four waves)
-    const float2* urow = a.u + (((t < te ? t : tb) / a.t_cal) * a.F + f) * int64_t(a.Na);
+    // stage E' of this frame (its four waves; zero past the last sample)
+    const float2* urow = a.u + (interval.at(t < te ? t : te - 1) * a.F + f) * int64_t(a.Na);
     float2 uu[APT];
     static_for<0, APT>([&](auto ic) {
-      const int an = gt + 256 * decltype(ic)::value;
-      uu[decltype(ic)::value] = gload(urow + (an < a.Na ? an : a.Na - 1));
+      constexpr int i = decltype(ic)::value;
+      if (has(i)) uu[i] = gload_at<float2>(urow, 8u * uint32_t(ant(i)));
     });
     static_for<0, APT>([&](auto ic) {
-      const int an = gt + 256 * decltype(ic)::value;
-      if (an < a.Na) epr[an] = t < te ? cmul(unpack_raw(Raw{raw[decltype(ic)::value], 0u}, FMT),
-                                             uu[decltype(ic)::value])
-                                      : make_float2(0.f, 0.f);
+      constexpr int i = decltype(ic)::value;
+      if (has(i)) epr[lam + 64 * ci + 256 * i] = t < te ? cmul(unpack_raw(raw[i], FMT), uu[i]) : make_float2(0.f, 0.f);
     });
     __syncthreads();
     grid_cls_half_fit<R>(H, epr, tw, stab, S0, 0, cx, cy, lam);
@@ -341,8 +312,8 @@ __device__ __forceinline__ void image_cls_pair_item(const ImageArgs& a, int f, i
 }
 
 // ---------------------------------------------------------------------------
-// Residue-class engine with two waves per SIMD for dense arrays (integer
-// E-fields; 513..2048 antennas at 256 x 256, up to 1024 at 128 x 128).
+// Residue-class engine with two waves per SIMD for dense arrays (513..2048
+// antennas at 256 x 256, up to 1024 at 128 x 128).
 //
 // Eight waves, one class each: at R = 4 the eight classes (cy = 2 cg + j,
 // j = 0, 1; cx = 0..3) of one frame, at R = 2 the four classes of two frames
@@ -363,9 +334,8 @@ __device__ __forceinline__ void image_cls_pair_item(const ImageArgs& a, int f, i
 // every workgroup of the array: cache resident), each batch of entries
 // requested while the previous one is gridded.  Workgroup barriers order the
 // staging, the two gridding passes and the row loads.
-// Multi-class slot code: antenna | qx << 12 | qy << 18 | px << 24 | py << 26
-//                        | last << 30 | first << 31
-// (padding slots: weight 0, first and not last, never stored).
+// Slot codes: cls_slot, marked on a sub-cell's last contribution (padding
+// slots: weight 0, first and not last, never stored).
 // ---------------------------------------------------------------------------
 constexpr int kClsDenseThreads = 512;
 
@@ -420,26 +390,25 @@ __device__ __forceinline__ void grid_dense_half(float2* H0, const float2* epr, c
     static_for<0, B>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       const uint32_t code = e[k].x;
-      const int qx = (code >> 12) & 63, qy = (code >> 18) & 63;
-      const int jx = qx + 64 * int((code >> 24) & 3), jy = qy + 64 * int((code >> 26) & 3);
-      const float2 ev = epr[code & kSlotAntMask];
+      const uint32_t jy = cls_slot_y(code);
+      const float2 ev = lds_at(epr, code & kClsAnt8Mask);
       float2 tx[R], ty[NCY];
       // tx[m] = e^{+2 pi i jx m / N}: one gather, the higher powers by products
-      tx[1] = tw[jx & (N - 1)];
+      tx[1] = tw[cls_slot_x(code)];
       static_for<2, R>([&](auto mc) {
         constexpr int m = decltype(mc)::value;
         tx[m] = cmul(tx[m - 1], tx[1]);
       });
       static_for<0, NCY>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        ty[j] = tw[(jy * (cy0 + j)) & (N - 1)];
+        ty[j] = lds_at(tw, __umul24(jy, 8u * uint32_t(cy0 + j)) & (8u * N - 8u));
       });
-      const float w = __uint_as_float(e[k].y);
+      const float w = fabsf(__uint_as_float(e[k].y));
       const float2 z = make_float2(w * ev.x, w * ev.y);
       // a cell's first contribution restarts its sums: acc * 0 + c, one FMA
       // per component instead of an add and a select
-      const float keep = int(code) < 0 ? 0.f : 1.f;
-      const bool last = (code >> 30) & 1;
+      const float keep = int(e[k].y) < 0 ? 0.f : 1.f;
+      const bool last = cls_slot_mark(code);
       static_for<0, NCY>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         const float2 zy = cmul(z, ty[j]);
@@ -453,7 +422,7 @@ __device__ __forceinline__ void grid_dense_half(float2* H0, const float2* epr, c
         });
       });
       if (last && s0 + k < S) {
-        const int off = qy * kHalfPitch + qx - 32 * hf;
+        const uint32_t off = (jy & 63u) * kHalfPitch + (cls_slot_x(code) & 31u);
         static_for<0, NCY>([&](auto jc) {
           static_for<0, R>([&](auto mc) {
             constexpr int j = decltype(jc)::value, m = decltype(mc)::value;
@@ -468,22 +437,21 @@ __device__ __forceinline__ void grid_dense_half(float2* H0, const float2* epr, c
 // GB: gridding slots per batch (2 or 4, an autotuner choice).
 template <int R, int FMT, int GB>
 __device__ __forceinline__ void image_cls_dense_item(const ImageArgs& a, int f, int cg, int s, uint8_t* smem) {
-  static_assert(FMT == kCI4 || FMT == kCI8, "integer E-field formats");
   using L = ClsDenseSmem<R>;
   constexpr int N = 64 * R, NF = L::NF, CPW = L::CPW, OW = L::OWNERS;
   constexpr int APT = L::MAXA / OW;                 // antennas per staging thread
   float2* lds = reinterpret_cast<float2*>(smem);
-  const int tid = threadIdx.x, lam = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lam = tid & 63, wave = wave_index();
   const int fs = wave / CPW, ci = wave % CPW;       // frame slot, class within the frame
   const int cx = ci % R, cy = cg * L::NCY + ci / R, cy0 = cg * L::NCY;
-  const int owner = tid % OW;                       // sub-cell owner (and staging thread) of the frame
+  const int owner = lam + 64 * ci;                     // sub-cell owner (and staging thread) of the frame
   float2* H = lds + wave * L::HALF;
   float2* H0 = lds + fs * CPW * L::HALF;            // the frame's first class buffer
   float2* epr = reinterpret_cast<float2*>(smem + L::E_OFF) + fs * L::MAXA;
   float2* tw = reinterpret_cast<float2*>(smem + L::TW_OFF);
   const int S0 = a.n_slots_m0, S1 = a.n_slots_m1;
   const int64_t tb = a.n_t * s / a.splits, te = a.n_t * (s + 1) / a.splits;
-  constexpr int bpe = FMT == kCI4 ? 1 : 2;
+  constexpr int bpe = FMT == kCF32 ? 8 : FMT == kCI8 ? 2 : 1;
 
   for (int k = tid; k < N; k += kClsDenseThreads) {
     double sn, cs;
@@ -495,29 +463,34 @@ __device__ __forceinline__ void image_cls_dense_item(const ImageArgs& a, int f, 
   float acc[64];
   static_for<0, 64>([&](auto yc) { acc[decltype(yc)::value] = 0.f; });
   float2 v[64];
-  uint32_t raw[APT];
+  Raw raw[APT];
+  // antennas owner + OW i of the frame's waves (lanes past the last antenna
+  // repeat it into staging entries that no slot refers to)
+  auto ant = [&](int own, int i) { return min(own + OW * i, a.Na - 1); };
   auto fetch_raw = [&](int64_t t) {
-    const uint8_t* row = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
+    const uint8_t* row = a.efield + ((t < te ? t : tb) * a.F + f) * int64_t(a.Na) * bpe;
+    const int own = opaque(owner);
     static_for<0, APT>([&](auto ic) {
-      const int an = owner + OW * decltype(ic)::value;
-      raw[decltype(ic)::value] = (t < te && an < a.Na) ? load_raw_global(row, an, FMT).x : 0u;
+      constexpr int i = decltype(ic)::value;
+      raw[i] = load_raw_global(row, ant(own, i), FMT);
     });
   };
+  static_for<0, APT>([&](auto ic) { raw[decltype(ic)::value] = Raw{0u, 0u}; });
   const int64_t iters = (te - tb + NF - 1) / NF;
+  IntervalCursor interval(a.t_cal);
   fetch_raw(tb + fs);
   for (int64_t it = 0; it < iters; ++it) {
     const int64_t t = tb + NF * it + fs;
-    const float2* urow = a.u + (((t < te ? t : tb) / a.t_cal) * a.F + f) * int64_t(a.Na);
+    const float2* urow = a.u + (interval.at(t < te ? t : te - 1) * a.F + f) * int64_t(a.Na);
+    const int own = opaque(owner);
     float2 uu[APT];
     static_for<0, APT>([&](auto ic) {
-      const int an = owner + OW * decltype(ic)::value;
-      uu[decltype(ic)::value] = gload(urow + (an < a.Na ? an : a.Na - 1));
+      constexpr int i = decltype(ic)::value;
+      uu[i] = gload_at<float2>(urow, 8u * uint32_t(ant(own, i)));
     });
     static_for<0, APT>([&](auto ic) {
-      const int an = owner + OW * decltype(ic)::value;
-      if (an < a.Na) epr[an] = t < te ? cmul(unpack_raw(Raw{raw[decltype(ic)::value], 0u}, FMT),
-                                             uu[decltype(ic)::value])
-                                      : make_float2(0.f, 0.f);
+      constexpr int i = decltype(ic)::value;
+      epr[own + OW * i] = t < te ? cmul(unpack_raw(raw[i], FMT), uu[i]) : make_float2(0.f, 0.f);
     });
     __syncthreads();                 // E' staged (and every half frame clear)
     grid_dense_half<R, GB>(H0, epr, tw, a.slots_m, S0, 0, cy0, owner);

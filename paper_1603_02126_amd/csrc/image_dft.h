@@ -446,15 +446,14 @@ __device__ __forceinline__ void dft_cls_item(const ImageArgs& a, int f, int cp, 
       for (int k = 0; k < S; ++k) {
         const uint2 e = gload(a.slots_c + k * OW + owner);
         const uint32_t code = e.x;
-        const int qx = (code >> 12) & 63, qy = (code >> 18) & 63;
-        const int jx = qx + 64 * int((code >> 24) & 3), jy = qy + 64 * int((code >> 26) & 3);
+        const int jx = int(cls_slot_x(code)), jy = int(cls_slot_y(code)), qx = jx & 63, qy = jy & 63;
         const float2 ph = tw[(jx * cx + jy * cy) & (N - 1)];
-        const float w = __uint_as_float(e.y);
-        const float2 ev = cmul(epr[code & kSlotAntMask], make_float2(w * ph.x, w * ph.y));
-        const float keep = int(code) < 0 ? 0.f : 1.f;   // a cell's first contribution restarts the sum
+        const float w = fabsf(__uint_as_float(e.y));
+        const float2 ev = cmul(lds_at(epr, code & kClsAnt8Mask), make_float2(w * ph.x, w * ph.y));
+        const float keep = int(e.y) < 0 ? 0.f : 1.f;   // a cell's first contribution restarts the sum
         sum.x = fmaf(sum.x, keep, ev.x);
         sum.y = fmaf(sum.y, keep, ev.y);
-        if ((code >> 30) & 1) {
+        if (cls_slot_mark(code)) {
           gt[qx * P + qy] = sum;
           mx = fmaxf(mx, fmaxf(fabsf(sum.x), fabsf(sum.y)));
         }

@@ -95,8 +95,12 @@ namespace epic {
 //   * after the row FFTs the frame is transposed (xpose.h) through the same
 //     half buffer, one component at a time, which leaves it zero;
 //   * column FFTs and |X|^2 accumulation as in the one-wave engine.
-// Waves never wait for each other inside the frame loop.  Integer E-field
-// formats (ci4, ci8) with 129..256 antennas (four per lane).
+// Waves never wait for each other inside the frame loop.  Up to 256 antennas
+// (two or four per lane), every E-field format (51 antennas of float samples,
+// 64 channels x 1000: a run of 448 us with the one-wave engine, 301 us with
+// this one).  A wave's sample index, rows and interval are scalars and slots
+// are packed for seven vector instructions each (grid_frame): the LWA-shaped
+// run went from 4.85 to 4.72 ms.
 // ---------------------------------------------------------------------------
 constexpr int kPairThreads = 512;
 
@@ -117,43 +121,38 @@ struct PairSmem {
 template <int APL, int FMT>
 __device__ __forceinline__ void pair_frames(const ImageArgs& a, int f, int64_t tb, int64_t te, float (&acc)[64],
                                             float2* H, float2* epr, const uint2* stab, int lam, int wave) {
-  static_assert(FMT == kCI4 || FMT == kCI8, "integer E-field formats");
   constexpr int N = 64, INFLIGHT = 8;
   const int S0 = a.n_slots_h0, S1 = a.n_slots_h1;
   float2 v[N];
-  uint32_t raw[APL];   // integer formats only: one packed sample per register
-  const int64_t iters = (te - tb + INFLIGHT - 1) / INFLIGHT;
-  constexpr int bpe = FMT == kCI4 ? 1 : 2;
+  Raw raw[APL];   // a packed integer sample takes one register, a float sample two
+  constexpr int bpe = FMT == kCF32 ? 8 : FMT == kCI8 ? 2 : 1;
   // the packed samples of a frame are requested at the end of the previous
   // frame; u (constant over an interval, cache resident) is loaded when the
-  // frame is staged
+  // frame is staged.  Lanes past the last antenna repeat it into staging
+  // entries that no slot refers to.
   auto fetch_raw = [&](int64_t t) {
     const uint8_t* row = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      raw[decltype(ic)::value] = (t < te && an < a.Na) ? load_raw_global(row, an, FMT).x : 0u;
+      raw[decltype(ic)::value] = load_raw_global(row, min(lam + N * decltype(ic)::value, a.Na - 1), FMT);
     });
   };
-  fetch_raw(tb + wave);
-  for (int64_t it = 0; it < iters; ++it) {
-    const int64_t t = tb + it * INFLIGHT + wave;
+  IntervalCursor interval(a.t_cal);
+  if (tb + wave < te) fetch_raw(tb + wave);
+  for (int64_t t = tb + wave; t < te; t += INFLIGHT) {
     // the LDS-bound phases of staging and gridding run at a raised wave
     // priority so that they advance while the other wave of the SIMD is in an
     // FFT (raising it for the transpose as well measured slower)
     __builtin_amdgcn_s_setprio(1);
     // calibrate: all u loads are issued before any is used (one memory
     // latency per frame)
-    const float2* urow = a.u + (((t < te ? t : tb) / a.t_cal) * a.F + f) * int64_t(a.Na);
+    const float2* urow = a.u + (interval.at(t) * a.F + f) * int64_t(a.Na);
     float2 uu[APL];
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      uu[decltype(ic)::value] = gload(urow + (an < a.Na ? an : a.Na - 1));
+      uu[decltype(ic)::value] = gload_at<float2>(urow, 8u * uint32_t(min(lam + N * decltype(ic)::value, a.Na - 1)));
     });
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      if (an < a.Na) epr[an] = t < te ? cmul(unpack_raw(Raw{raw[decltype(ic)::value], 0u}, FMT),
-                                             uu[decltype(ic)::value])
-                                      : make_float2(0.f, 0.f);
+      constexpr int i = decltype(ic)::value;
+      epr[lam + N * i] = cmul(unpack_raw(raw[i], FMT), uu[i]);
     });
     wave_lds_sync();
     // columns 0..31: grid, every lane loads its row's half and clears it
@@ -172,7 +171,7 @@ __device__ __forceinline__ void pair_frames(const ImageArgs& a, int f, int64_t t
     fft_reg<N, +1>(v);            // along y
     // the next frame's samples are requested here rather than at staging:
     // their registers would otherwise stay live through both FFTs
-    fetch_raw(t + INFLIGHT);
+    fetch_raw(t + INFLIGHT < te ? t + INFLIGHT : t);
     add_norms<N>(acc, v);
   }
 }
@@ -205,7 +204,7 @@ __device__ __forceinline__ void pair_reduce(float (&acc)[64], float* out, float 
 template <int APL, int FMT>
 __device__ __forceinline__ void image_item_pair(const ImageArgs& a, int f, int s, uint8_t* smem) {
   using L = PairSmem<APL>;
-  const int lam = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lam = threadIdx.x & 63, wave = wave_index();
   float2* H = reinterpret_cast<float2*>(smem) + wave * L::WAVE;
   uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
   const int64_t tb = a.n_t * s / a.splits, te = a.n_t * (s + 1) / a.splits;
@@ -316,11 +315,10 @@ __device__ __forceinline__ void image_item_snap(const ImageArgs& a, int f, int s
 
 template <int APL, int FMT>
 __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, int s, uint8_t* smem) {
-  static_assert(FMT == kCI4 || FMT == kCI8, "integer E-field formats");
   constexpr int N = 64, INFLIGHT = 8;
   using L = PairSmem<APL>;
   float2* lds = reinterpret_cast<float2*>(smem);
-  const int lam = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lam = threadIdx.x & 63, wave = wave_index();
   float2* H = lds + wave * L::WAVE;
   float2* epr = H + L::HALF;
   uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
@@ -335,31 +333,29 @@ __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, 
   float acc[N];
   static_for<0, N>([&](auto yc) { acc[decltype(yc)::value] = 0.f; });
   float2 v[N];
-  uint32_t raw[APL];
-  constexpr int bpe = FMT == kCI4 ? 1 : 2;
-  auto fetch_raw = [&](const SnapCursor& c) {
-    const bool ok = c.valid();
-    const uint8_t* row = a.efield + (c.t() * a.F + f) * int64_t(a.Na) * bpe;
+  Raw raw[APL];
+  constexpr int bpe = FMT == kCF32 ? 8 : FMT == kCI8 ? 2 : 1;
+  auto fetch_raw = [&](const SnapCursor& c, const SnapCursor& last) {
+    const int64_t t = c.valid() ? c.t() : last.t();
+    const uint8_t* row = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      raw[decltype(ic)::value] = (ok && an < a.Na) ? load_raw_global(row, an, FMT).x : 0u;
+      raw[decltype(ic)::value] = load_raw_global(row, min(lam + N * decltype(ic)::value, a.Na - 1), FMT);
     });
   };
   // the waves are independent: each walks its own windows
   SnapCursor cur{wb + wave, 0, we, INFLIGHT, a.t_acc, a.n_t};
-  fetch_raw(cur);
+  IntervalCursor interval(a.t_cal);
+  if (cur.valid()) fetch_raw(cur, cur);
   while (cur.valid()) {
-    const int64_t t = cur.t();
     __builtin_amdgcn_s_setprio(1);
-    const float2* urow = a.u + ((t / a.t_cal) * a.F + f) * int64_t(a.Na);
+    const float2* urow = a.u + (interval.at(cur.t()) * a.F + f) * int64_t(a.Na);
     float2 uu[APL];
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      uu[decltype(ic)::value] = gload(urow + (an < a.Na ? an : a.Na - 1));
+      uu[decltype(ic)::value] = gload_at<float2>(urow, 8u * uint32_t(min(lam + N * decltype(ic)::value, a.Na - 1)));
     });
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      if (an < a.Na) epr[an] = cmul(unpack_raw(Raw{raw[decltype(ic)::value], 0u}, FMT), uu[decltype(ic)::value]);
+      constexpr int i = decltype(ic)::value;
+      epr[lam + N * i] = cmul(unpack_raw(raw[i], FMT), uu[i]);
     });
     wave_lds_sync();
     grid_frame_fit(H, epr, stab, S0, N, lam);
@@ -376,7 +372,7 @@ __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, 
     fft_reg<N, +1>(v);
     SnapCursor nxt = cur;
     nxt.next();
-    fetch_raw(nxt);
+    fetch_raw(nxt, cur);
     add_norms<N>(acc, v);
     if (cur.last()) snap_store<N>(a, f, cur.j, acc, lam);
     cur = nxt;
@@ -390,7 +386,7 @@ __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, 
 template <int APL, int FMT>
 __device__ __forceinline__ void image_item_pair_snap_group(const ImageArgs& a, int f, int s, uint8_t* smem) {
   using L = PairSmem<APL>;
-  const int lam = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lam = threadIdx.x & 63, wave = wave_index();
   float2* H = reinterpret_cast<float2*>(smem) + wave * L::WAVE;
   uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
   const int64_t W = (a.n_t + a.t_acc - 1) / a.t_acc;

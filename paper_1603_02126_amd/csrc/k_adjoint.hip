@@ -111,22 +111,23 @@ __global__ __launch_bounds__(256) void k_adjoint(AdjointArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// The same adjoint with two waves per SIMD (64 x 64, integer E-fields, 129..256
-// antennas), built like the paired imaging engine: eight waves per
+// The same adjoint with two waves per SIMD (64 x 64, up to 256 antennas), built like the paired imaging engine: eight waves per
 // workgroup, each imaging its own frames through half a frame (columns 0..31,
 // then 32..63) and transposing through that half buffer (xpose.h).  After R and the conjugate
 // transform the frame G' (lane = row y) goes back through the same half
 // buffer, one half of the columns at a time, and each lane gathers its
 // antennas' kernel cells of that half (the other half's cells carry weight
-// zero).  R is read per frame from the cache (16 KiB per channel).
+// zero).  R is read per frame from the cache (16 KiB per channel).  Integer
+// samples stay in registers from the staging to the correlation; float samples
+// (twice the registers) are read again, from the cache, with the cell tables.
 // ---------------------------------------------------------------------------
-template <int FMT>
+template <int FMT, int APL>
 __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
-  static_assert(FMT == kCI4 || FMT == kCI8, "integer E-field formats");
-  constexpr int N = 64, APL = 4, K2 = 4, INFLIGHT = 8;
+  constexpr int N = 64, K2 = 4, INFLIGHT = 8;
+  constexpr bool REREAD = FMT == kCF32;
   using L = PairSmem<APL>;
   __shared__ __align__(16) uint8_t smem[L::BYTES];
-  const int lam = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lam = threadIdx.x & 63, wave = wave_index();
   float2* H = reinterpret_cast<float2*>(smem) + wave * L::WAVE;
   float2* epr = H + L::HALF;
   uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
@@ -140,27 +141,23 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
   __syncthreads();
   // per frame (cache resident, loaded where used: the loop has no registers
   // to keep them): the fixed calibration u and, for antenna lam + 64 i and
-  // kernel cell k, the cell's offset in the half buffer (bit 15: the half of
-  // the columns it lies in) and its weight
+  // kernel cell k, the cell's byte offset in the half buffer (bit 16: the half
+  // of the columns it lies in) and its weight
   const float2* urow = a.u + int64_t(f) * a.Na;
 
   double2 du[APL];
   static_for<0, APL>([&](auto ic) { du[decltype(ic)::value] = make_double2(0.0, 0.0); });
   float2 v[N];
-  uint32_t raw[APL], rawc[APL];
-  constexpr int bpe = FMT == kCI4 ? 1 : 2;
+  Raw raw[APL], rawc[APL];
+  constexpr int bpe = FMT == kCF32 ? 8 : FMT == kCI8 ? 2 : 1;
   auto fetch_raw = [&](int64_t t) {
     const uint8_t* row = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
     static_for<0, APL>([&](auto ic) {
-      const int an = lam + N * decltype(ic)::value;
-      raw[decltype(ic)::value] = (t < te && an < a.Na) ? load_raw_global(row, an, FMT).x : 0u;
+      raw[decltype(ic)::value] = load_raw_global(row, min(lam + N * decltype(ic)::value, a.Na - 1), FMT);
     });
   };
-  const int64_t iters = (te - tb + INFLIGHT - 1) / INFLIGHT;
-  fetch_raw(tb + wave);
-  for (int64_t it = 0; it < iters; ++it) {
-    const int64_t t = tb + it * INFLIGHT + wave;
-    const bool active = t < te;
+  if (tb + wave < te) fetch_raw(tb + wave);
+  for (int64_t t = tb + wave; t < te; t += INFLIGHT) {
     __builtin_amdgcn_s_setprio(1);
     // per-frame addresses come from an opaque copy of the lane index: hoisted
     // out of the loop as invariants they would occupy ~80 registers
@@ -168,14 +165,12 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
     asm volatile("" : "+v"(lo));
     float2 uu[APL];
     static_for<0, APL>([&](auto ic) {
-      const int an = lo + N * decltype(ic)::value;
-      uu[decltype(ic)::value] = gload(urow + (an < a.Na ? an : a.Na - 1));
+      uu[decltype(ic)::value] = gload_at<float2>(urow, 8u * uint32_t(min(lo + N * decltype(ic)::value, a.Na - 1)));
     });
     static_for<0, APL>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      const int an = lam + N * i;
-      rawc[i] = raw[i];
-      if (an < a.Na) epr[an] = active ? cmul(unpack_raw(Raw{raw[i], 0u}, FMT), uu[i]) : make_float2(0.f, 0.f);
+      if constexpr (!REREAD) rawc[i] = raw[i];
+      epr[lam + N * i] = cmul(unpack_raw(raw[i], FMT), uu[i]);
     });
     wave_lds_sync();
     grid_frame<8>(H, epr, stab, S0, N, lam);
@@ -192,7 +187,7 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
     transpose64(v, H, lam);       // lane = column kx
     __builtin_amdgcn_s_setprio(0);
     fft_reg<N, +1>(v);            // along y: v[ky] = X(kx = lane, ky)
-    fetch_raw(t + INFLIGHT);
+    fetch_raw(t + INFLIGHT < te ? t + INFLIGHT : t);
     // the loads below stay in their phase: hoisted above the transforms they
     // would hold registers that the transforms need
     __builtin_amdgcn_sched_barrier(0);
@@ -201,7 +196,7 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
     static_for<0, 4>([&](auto cc) {
       constexpr int c0 = 16 * decltype(cc)::value;
       float rr[16];
-      static_for<0, 16>([&](auto kc) { rr[decltype(kc)::value] = gload(Rf + (c0 + decltype(kc)::value) * N + lr); });
+      static_for<0, 16>([&](auto kc) { rr[decltype(kc)::value] = gload_at<float>(Rf + (c0 + decltype(kc)::value) * N, 4u * uint32_t(lr)); });
       static_for<0, 16>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         v[c0 + k] = cscale(v[c0 + k], rr[k]);
@@ -220,16 +215,17 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
     float dw[APL][K2];
     int ld = lam;
     asm volatile("" : "+v"(ld));
+    // (a lane past the last antenna gathers cell 0 with weight zero)
+    const uint8_t* rowc = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
     static_for<0, APL>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
       const int an = ld + N * i;
+      if constexpr (REREAD) rawc[i] = load_raw_global(rowc, min(an, a.Na - 1), FMT);
       static_for<0, K2>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        const int q = (an < a.Na ? an : 0) * K2 + k;
-        const uint32_t ixy = gload(a.cell_ixy + q);
-        const int ix = int(ixy & 0xffffu), iy = int(ixy >> 16);
-        doff[i][k] = iy * kHalfPitch + (ix & 31) + ((ix >> 5) << 15);
-        dw[i][k] = an < a.Na ? gload(a.cell_w + q) : 0.f;
+        const uint2 q = gload_at<uint2>(a.degrid + (i * K2 + k) * N, 8u * uint32_t(ld));
+        doff[i][k] = int(q.x);
+        dw[i][k] = __uint_as_float(q.y);
       });
     });
     float2 gb[APL];
@@ -242,8 +238,8 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
         constexpr int i = decltype(ic)::value;
         static_for<0, K2>([&](auto kc) {
           constexpr int k = decltype(kc)::value;
-          const float2 c = H[doff[i][k] & 0x7fff];
-          const float w = (doff[i][k] >> 15) == hf ? dw[i][k] : 0.f;
+          const float2 c = lds_at(H, uint32_t(doff[i][k]) & 0xffffu);
+          const float w = (doff[i][k] >> 16) == hf ? dw[i][k] : 0.f;
           gb[i].x = fmaf(w, c.x, gb[i].x);
           gb[i].y = fmaf(w, c.y, gb[i].y);
         });
@@ -255,8 +251,8 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
     // correlate with the uncalibrated E-field: du_a += conj(E_a) G'(cells of a)
     static_for<0, APL>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      if (active && lam + N * i < a.Na) {
-        const float2 e = unpack_raw(Raw{rawc[i], 0u}, FMT);
+      if (lam + N * i < a.Na) {
+        const float2 e = unpack_raw(rawc[i], FMT);
         du[i].x += double(e.x * gb[i].x + e.y * gb[i].y);
         du[i].y += double(e.x * gb[i].y - e.y * gb[i].x);
       }
@@ -317,11 +313,12 @@ __global__ __launch_bounds__(256) void k_recip(const double2* gains, const uint8
 template <int N, int APL>
 struct LaunchAdjoint {
   static hipError_t run(const AdjointArgs& a, hipStream_t s) {
-    if constexpr (N == 64 && APL == 4) {
-      if (a.fmt != kCF32 && a.slots_h && a.n_slots_h0 + a.n_slots_h1 <= PairSmem<4>::TAB_SLOTS && a.k2 <= 4) {
+    if constexpr (N == 64 && (APL == 2 || APL == 4)) {
+      if (a.slots_h && a.degrid && a.n_slots_h0 + a.n_slots_h1 <= PairSmem<APL>::TAB_SLOTS && a.k2 <= 4) {
         const dim3 grid(a.F * a.splits), block(kPairThreads);
-        if (a.fmt == kCI4) hipLaunchKernelGGL((k_adjoint_pair<kCI4>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_adjoint_pair<kCI8>), grid, block, 0, s, a);
+        with_format(a.fmt, [&](auto fc) {
+          hipLaunchKernelGGL((k_adjoint_pair<decltype(fc)::value, APL>), grid, block, 0, s, a);
+        });
         return hipGetLastError();
       }
     }

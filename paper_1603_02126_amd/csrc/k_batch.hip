@@ -55,7 +55,6 @@ __global__ __launch_bounds__(kBatchThreads) void k_image_batch(BatchImageArgs b)
 
 int batch_body(const ImageArgs& a, int N, bool dft) {
   if (dft) return 0;
-  const bool integer = a.fmt == kCI4 || a.fmt == kCI8;
   if (N == 16 || N == 32) {
     const int apl = apl_for(N, a.Na);
     const int cap = N == 16 ? (apl == 2 ? Budget<16, 2, 8>::TAB_SLOTS : apl == 4 ? Budget<16, 4, 8>::TAB_SLOTS
@@ -65,7 +64,7 @@ int batch_body(const ImageArgs& a, int N, bool dft) {
     return fft8_code(N, apl);
   }
   if (N == 64) return pair_engine(a, N) ? pair_code(apl_for(N, a.Na), a.fmt) : 0;
-  if ((N == 128 || N == 256) && integer) {
+  if (N == 128 || N == 256) {
     const int R = N / 64;
     if (cls_pair_engine(a, N)) return cls_pair_code(R, a.fmt, cls_pair_db(a, N));
     if (cls_dense_engine(a, N)) return dense_code(R, a.fmt, a.grid_batch == 4 ? 4 : 2);

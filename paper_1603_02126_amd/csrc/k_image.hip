@@ -66,14 +66,6 @@ __global__ __launch_bounds__(kPairThreads) void k_image_pair_snap_group(ImageArg
   image_item_pair_snap_group<APL, FMT>(a, blockIdx.x % a.F, blockIdx.x / a.F, smem);
 }
 
-template <int R>
-__global__ __launch_bounds__(256) void k_image_cls(ImageArgs a) {
-  __shared__ __align__(16) uint8_t smem[ClsSmem<R, false>::BYTES];
-  constexpr int CG = (R * R) / 4;
-  const int rest = blockIdx.x / a.F;
-  image_cls_item<R, false>(a, blockIdx.x % a.F, rest % CG, rest / CG, smem);
-}
-
 template <int R, int FMT, bool DB>
 __global__ __launch_bounds__(kClsPairThreads) void k_image_cls_pair(ImageArgs a) {
   __shared__ __align__(16) uint8_t smem[ClsPairSmem<R, DB>::BYTES];
@@ -92,10 +84,10 @@ __global__ __launch_bounds__(kClsDenseThreads) void k_image_cls_dense(ImageArgs 
 
 template <int R>
 __global__ __launch_bounds__(256) void k_image_cls_big(ImageArgs a) {
-  __shared__ __align__(16) uint8_t smem[ClsSmem<R, true>::BYTES];
+  __shared__ __align__(16) uint8_t smem[ClsBigSmem<R>::BYTES];
   constexpr int CG = (R * R) / 4;
   const int rest = blockIdx.x / a.F;
-  image_cls_item<R, true>(a, blockIdx.x % a.F, rest % CG, rest / CG, smem);
+  image_cls_big_item<R>(a, blockIdx.x % a.F, rest % CG, rest / CG, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -136,27 +128,19 @@ hipError_t launch_unpack(const uint8_t* efield, int64_t n, int fmt, int16_t* out
 int grid_lanes(int N) { return N; }
 int grid_pitch(int N) { return N + 2; }
 
-int cls_table_slots() { return kClsTabSlots; }
-
-// 1: slot table in LDS, 2: dense-array variant, 0: unsupported
-int cls_variant(int na, int n_slots) {
-  if (na <= kClsMaxAnt && n_slots <= kClsTabSlots) return 1;
-  return na <= kClsMaxAntBig ? 2 : 0;
-}
-
 bool image_supported(int N, int na, int n_slots) {
-  if (N == 128 || N == 256) return cls_variant(na, n_slots) != 0;
+  if (N == 128 || N == 256) return na <= kClsMaxAntBig;
   if (!(N == 16 || N == 32 || N == 64) || na > 8 * N) return false;
   const int apl = apl_for(N, na);
   return apl != 0 && n_slots <= tab_slots_for(N, apl);
 }
 
-// The paired 64 x 64 engine: integer E-fields, up to 256 antennas (two or
-// four per lane: the register budget of two waves per SIMD is checked
-// there), and a half-frame schedule that fits its LDS table.
+// The paired 64 x 64 engine: up to 256 antennas (two or four per lane: the
+// register budget of two waves per SIMD is checked there), and a half-frame
+// schedule that fits its LDS table.
 bool pair_engine(const ImageArgs& a, int N) {
   const int apl = apl_for(N, a.Na);
-  return N == 64 && a.fmt != kCF32 && (apl == 2 || apl == 4) && a.slots_h != nullptr &&
+  return N == 64 && (apl == 2 || apl == 4) && a.slots_h != nullptr &&
          a.n_slots_h0 + a.n_slots_h1 <= (apl == 2 ? PairSmem<2>::TAB_SLOTS : PairSmem<4>::TAB_SLOTS);
 }
 
@@ -165,8 +149,10 @@ struct LaunchImage {
   static hipError_t run(const ImageArgs& a, hipStream_t s) {
     if constexpr (N == 64 && (APL == 2 || APL == 4)) {
       if (pair_engine(a, N)) {
-        if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_pair<APL, kCI4>), dim3(a.F * a.splits), dim3(kPairThreads), 0, s, a);
-        else hipLaunchKernelGGL((k_image_pair<APL, kCI8>), dim3(a.F * a.splits), dim3(kPairThreads), 0, s, a);
+        with_format(a.fmt, [&](auto fc) {
+          constexpr int FMT = decltype(fc)::value;
+          hipLaunchKernelGGL((k_image_pair<APL, FMT>), dim3(a.F * a.splits), dim3(kPairThreads), 0, s, a);
+        });
         return hipGetLastError();
       }
     }
@@ -175,28 +161,27 @@ struct LaunchImage {
   }
 };
 
-// The residue-class engine with two waves per SIMD: integer E-fields, at
-// most 512 antennas, half-frame schedules that fit its LDS table; with at
-// most kClsPairMaxAntDB antennas and a table that still fits, its
-// double-buffered form (one barrier per pair of samples).
+// The residue-class engine with two waves per SIMD: at most 512 antennas,
+// half-frame schedules that fit its LDS table; with at most kClsPairMaxAntDB
+// antennas and a table that still fits, its double-buffered form (one barrier
+// per pair of samples).
 bool cls_pair_db(const ImageArgs& a, int N) {
   const int cap = N == 128 ? ClsPairSmem<2, true>::TAB_SLOTS : ClsPairSmem<4, true>::TAB_SLOTS;
   return a.Na <= kClsPairMaxAntDB && a.n_slots_h0 + a.n_slots_h1 <= cap;
 }
 
 bool cls_pair_engine(const ImageArgs& a, int N) {
-  if (!(N == 128 || N == 256) || a.fmt == kCF32 || a.Na > kClsMaxAnt || !a.slots_h || a.grid_batch != 0)
-    return false;
+  if (!(N == 128 || N == 256) || a.Na > kClsMaxAnt || !a.slots_h || a.grid_batch != 0) return false;
   const int cap = N == 128 ? ClsPairSmem<2>::TAB_SLOTS : ClsPairSmem<4>::TAB_SLOTS;
   return a.n_slots_h0 + a.n_slots_h1 <= cap;
 }
 
-// The dense residue-class engine with two waves per SIMD: integer E-fields,
-// up to 2048 antennas at 256 x 256 and 1024 at 128 x 128 (its E' staging of
-// one or two frames); by default the arrays the class-pair engine does not
-// take, any of them when a gridding batch is chosen (grid_batch 2 or 4).
+// The dense residue-class engine with two waves per SIMD: up to 2048 antennas
+// at 256 x 256 and 1024 at 128 x 128 (its E' staging of one or two frames); by
+// default the arrays the class-pair engine does not take, any of them when a
+// gridding batch is chosen (grid_batch 2 or 4).
 bool cls_dense_engine(const ImageArgs& a, int N) {
-  if (!(N == 128 || N == 256) || a.fmt == kCF32 || !a.slots_m || cls_pair_engine(a, N)) return false;
+  if (!(N == 128 || N == 256) || !a.slots_m || cls_pair_engine(a, N)) return false;
   return a.Na <= (N == 256 ? ClsDenseSmem<4>::MAXA : ClsDenseSmem<2>::MAXA);
 }
 
@@ -205,46 +190,36 @@ int cls_groups(const ImageArgs& a, int N) {
   return 1;
 }
 
-hipError_t launch_image(int N, const ImageArgs& a, hipStream_t s) {
-  if (N == 128 || N == 256) {
-    const bool big = cls_variant(a.Na, a.n_slots) == 2;
-    const dim3 grid(a.F * cls_groups(a, N) * a.splits);
-    if (cls_dense_engine(a, N)) {
-      const dim3 blk(kClsDenseThreads);
-      if (a.grid_batch == 4) {
-        if (N == 128 && a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_dense<2, kCI4, 4>), grid, blk, 0, s, a);
-        else if (N == 128) hipLaunchKernelGGL((k_image_cls_dense<2, kCI8, 4>), grid, blk, 0, s, a);
-        else if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_dense<4, kCI4, 4>), grid, blk, 0, s, a);
-        else hipLaunchKernelGGL((k_image_cls_dense<4, kCI8, 4>), grid, blk, 0, s, a);
-      } else {
-        if (N == 128 && a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_dense<2, kCI4, 2>), grid, blk, 0, s, a);
-        else if (N == 128) hipLaunchKernelGGL((k_image_cls_dense<2, kCI8, 2>), grid, blk, 0, s, a);
-        else if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_dense<4, kCI4, 2>), grid, blk, 0, s, a);
-        else hipLaunchKernelGGL((k_image_cls_dense<4, kCI8, 2>), grid, blk, 0, s, a);
-      }
-      return hipGetLastError();
-    }
-    if (cls_pair_engine(a, N)) {
-      const dim3 blk(kClsPairThreads);
-      if (cls_pair_db(a, N)) {
-        if (N == 128 && a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_pair<2, kCI4, true>), grid, blk, 0, s, a);
-        else if (N == 128) hipLaunchKernelGGL((k_image_cls_pair<2, kCI8, true>), grid, blk, 0, s, a);
-        else if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_pair<4, kCI4, true>), grid, blk, 0, s, a);
-        else hipLaunchKernelGGL((k_image_cls_pair<4, kCI8, true>), grid, blk, 0, s, a);
-      } else {
-        if (N == 128 && a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_pair<2, kCI4, false>), grid, blk, 0, s, a);
-        else if (N == 128) hipLaunchKernelGGL((k_image_cls_pair<2, kCI8, false>), grid, blk, 0, s, a);
-        else if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_cls_pair<4, kCI4, false>), grid, blk, 0, s, a);
-        else hipLaunchKernelGGL((k_image_cls_pair<4, kCI8, false>), grid, blk, 0, s, a);
-      }
-      return hipGetLastError();
-    }
-    if (N == 128 && !big) hipLaunchKernelGGL((k_image_cls<2>), grid, dim3(256), 0, s, a);
-    else if (N == 128) hipLaunchKernelGGL((k_image_cls_big<2>), grid, dim3(256), 0, s, a);
-    else if (!big) hipLaunchKernelGGL((k_image_cls<4>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_image_cls_big<4>), grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+// The residue-class engines (R = N / 64): the class-pair engine, the dense
+// one, and for what neither takes (128 x 128 above 1024 antennas) the one-wave
+// engine.
+template <int R>
+static hipError_t launch_image_cls(const ImageArgs& a, hipStream_t s) {
+  constexpr int N = 64 * R;
+  const dim3 grid(a.F * cls_groups(a, N) * a.splits);
+  if (cls_dense_engine(a, N)) {
+    with_format(a.fmt, [&](auto fc) {
+      constexpr int FMT = decltype(fc)::value;
+      if (a.grid_batch == 4) hipLaunchKernelGGL((k_image_cls_dense<R, FMT, 4>), grid, dim3(kClsDenseThreads), 0, s, a);
+      else hipLaunchKernelGGL((k_image_cls_dense<R, FMT, 2>), grid, dim3(kClsDenseThreads), 0, s, a);
+    });
+  } else if (cls_pair_engine(a, N)) {
+    with_format(a.fmt, [&](auto fc) {
+      constexpr int FMT = decltype(fc)::value;
+      if (cls_pair_db(a, N)) hipLaunchKernelGGL((k_image_cls_pair<R, FMT, true>), grid, dim3(kClsPairThreads), 0, s, a);
+      else hipLaunchKernelGGL((k_image_cls_pair<R, FMT, false>), grid, dim3(kClsPairThreads), 0, s, a);
+    });
+  } else if constexpr (R == 2) {
+    hipLaunchKernelGGL((k_image_cls_big<R>), grid, dim3(256), 0, s, a);
+  } else {
+    return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_image(int N, const ImageArgs& a, hipStream_t s) {
+  if (N == 128) return launch_image_cls<2>(a, s);
+  if (N == 256) return launch_image_cls<4>(a, s);
   return dispatch_n<LaunchImage>(N, a.Na, a, s);
 }
 
@@ -254,13 +229,11 @@ struct LaunchImageSnap {
     if constexpr (N == 64 && (APL == 2 || APL == 4)) {
       if (pair_engine(a, N)) {
         const dim3 grid(a.F * a.splits), block(kPairThreads);
-        if (a.t_acc >= kSnapGroupWindow) {
-          if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_pair_snap_group<APL, kCI4>), grid, block, 0, s, a);
-          else hipLaunchKernelGGL((k_image_pair_snap_group<APL, kCI8>), grid, block, 0, s, a);
-        } else {
-          if (a.fmt == kCI4) hipLaunchKernelGGL((k_image_pair_snap<APL, kCI4>), grid, block, 0, s, a);
-          else hipLaunchKernelGGL((k_image_pair_snap<APL, kCI8>), grid, block, 0, s, a);
-        }
+        with_format(a.fmt, [&](auto fc) {
+          constexpr int FMT = decltype(fc)::value;
+          if (a.t_acc >= kSnapGroupWindow) hipLaunchKernelGGL((k_image_pair_snap_group<APL, FMT>), grid, block, 0, s, a);
+          else hipLaunchKernelGGL((k_image_pair_snap<APL, FMT>), grid, block, 0, s, a);
+        });
         return hipGetLastError();
       }
     }

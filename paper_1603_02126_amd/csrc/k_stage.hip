@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kPairThreads) void k_grid_half(GridArgs a) {
   constexpr int N = 64, W = kPairThreads / 64;
   using L = PairSmem<APL>;
   __shared__ __align__(16) uint8_t smem[L::BYTES];
-  const int lam = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lam = threadIdx.x & 63, wave = wave_index();
   float2* H = reinterpret_cast<float2*>(smem) + wave * L::WAVE;
   float2* epr = H + L::HALF;
   uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kAccThreads) void k_image_acc64(ImageAccArgs a) {
   constexpr int N = 64, W = kAccThreads / 64;
   __shared__ __align__(16) float2 lds[W * kXposeFloat2];
   static_assert(W * N * N * 4 <= W * kXposeFloat2 * 8, "the accumulator reduction reuses the staging areas");
-  const int lam = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lam = threadIdx.x & 63, wave = wave_index();
   const int f = blockIdx.x % a.F, s = blockIdx.x / a.F;
   const int tb = int(int64_t(a.nt) * s / a.splits), te = int(int64_t(a.nt) * (s + 1) / a.splits);
   float2* T = lds + wave * kXposeFloat2;
