@@ -215,10 +215,14 @@ __device__ __forceinline__ float2 lds_take(float2* p) {
   return make_float2(__uint_as_float(uint32_t(r)), __uint_as_float(uint32_t(r >> 32)));
 }
 
+template <int N, int X0>
+__device__ __forceinline__ void take_half_row_n(float2 (&v)[N], float2* H, int lam) {
+  float2* row = H + lam * half_pitch(N);
+  static_for<0, N / 2>([&](auto xc) { v[X0 + decltype(xc)::value] = lds_take(row + decltype(xc)::value); });
+}
 template <int X0>
 __device__ __forceinline__ void take_half_row(float2 (&v)[64], float2* H, int lam) {
-  float2* row = H + lam * kHalfPitch;
-  static_for<0, 32>([&](auto xc) { v[X0 + decltype(xc)::value] = lds_take(row + decltype(xc)::value); });
+  take_half_row_n<64, X0>(v, H, lam);
 }
 
 // Clears the lane's row of a half-frame buffer, pad column included.

@@ -226,8 +226,8 @@ void model_tables(const HostArray& h, const epic_model_desc* m, ModelTables& t, 
 // (transposed, the DFT-GEMM engine's: antenna | offset << 12 | first << 31, weight).
 // Padding slots store zero into the pad column (offset = grid size).
 // Returns the slot count S; table is [S][L] (lane fastest), 2 words each.
-// half >= 0: the columns 32 half <= x < 32 half + 32 only, at offsets
-// y * kHalfPitch + x - 32 half of the half-frame buffer (pad: column 32).
+// half >= 0: the columns nx/2 half <= x < nx/2 (half + 1) only, at offsets
+// y half_pitch(nx) + x - nx/2 half of the half-frame buffer (pad: column nx/2).
 int build_slots(const HostArray& h, int L, int pitch, std::vector<uint32_t>& table, bool transposed = false,
                 int half = -1) {
   std::vector<int32_t> ix, iy;
@@ -239,7 +239,7 @@ int build_slots(const HostArray& h, int L, int pitch, std::vector<uint32_t>& tab
     for (int k = 0; k < h.k2; ++k) {
       const size_t q = size_t(a) * h.k2 + k;
       if (w[q] == 0.0) continue;
-      if (half >= 0 && ix[q] / 32 != half) continue;
+      if (half >= 0 && ix[q] / (h.nx / 2) != half) continue;
       cell[size_t(iy[q]) * h.nx + ix[q]].push_back({a, float(w[q])});
     }
   }
@@ -258,7 +258,7 @@ int build_slots(const HostArray& h, int L, int pitch, std::vector<uint32_t>& tab
   }
   size_t S = 0;
   for (int l = 0; l < L; ++l) S = std::max(S, load[l]);
-  const uint32_t pad = uint32_t(half >= 0 ? 32 : h.nx);   // row 0, first pad column
+  const uint32_t pad = uint32_t(half >= 0 ? h.nx / 2 : h.nx);   // row 0, first pad column
   auto put = [&](size_t at, uint32_t ant, uint32_t off, float wf, bool first) {
     uint32_t wb;
     std::memcpy(&wb, &wf, 4);
@@ -275,7 +275,7 @@ int build_slots(const HostArray& h, int L, int pitch, std::vector<uint32_t>& tab
     size_t s = 0;
     for (int c : lane_cells[l]) {
       const int cy = c / h.nx, cx = c % h.nx;
-      const uint32_t off = half >= 0   ? uint32_t(cy * epic::kHalfPitch + cx - 32 * half)
+      const uint32_t off = half >= 0   ? uint32_t(cy * epic::half_pitch(h.nx) + cx - h.nx / 2 * half)
                            : transposed ? uint32_t(cx * pitch + cy)
                                         : uint32_t(cy * pitch + cx);
       const auto& lst = cell[c];
@@ -449,17 +449,25 @@ void* static_scratch_ptr(int dev, hipError_t* err) {
 // ---------------------------------------------------------------------------
 // plan
 // ---------------------------------------------------------------------------
+// The time splits last worked out for an array (pick_splits).
+struct SplitMemo {
+  int64_t T = -1;
+  uint64_t generation = 0;
+  int splits = 1;
+};
+
 struct ArrayPlan {
   HostArray h;
+  mutable SplitMemo memo[2];
   uint32_t* d_cell_ixy = nullptr;
   float* d_cell_w = nullptr;
   uint2* d_slots = nullptr;   // gridding schedule of the imaging engine
   int n_slots = 0;
   uint2* d_slots_dft = nullptr;   // schedule of the DFT-GEMM engine (64 lanes, G^T)
   int n_slots_dft = 0;
-  uint2* d_slots_h = nullptr;     // 64 x 64: half-frame schedule (two halves of rows)
+  uint2* d_slots_h = nullptr;     // half-frame schedules
   int n_slots_h0 = 0, n_slots_h1 = 0;
-  uint2* d_degrid = nullptr;      // 64 x 64, up to 256 antennas: degridding table (AdjointArgs)
+  uint2* d_degrid = nullptr;      // N <= 64: degridding table (AdjointArgs)
   uint2* d_slots_m = nullptr;     // 128 / 256: multi-class schedules (two halves)
   int n_slots_m0 = 0, n_slots_m1 = 0;
   uint2* d_slots_c = nullptr;     // 128 / 256: class schedule of the DFT-GEMM engine (128 owners)
@@ -709,13 +717,20 @@ ImageArgs engine_probe(const ArrayPlan& ap) {
 
 // Workgroups of one time split per channel (class groups of the N = 256 engines).
 int units_for(const ArrayPlan& ap) { return epic::cls_groups(engine_probe(ap), ap.h.nx); }
-// Frames a workgroup images at once.
-int slots_for(int N) { return N >= 128 ? 1 : 4 * (64 / N); }
-
 // What a time-split count is for: the separate imaging launch of a run or of
-// the stage-wise call, the fused solve + imaging launch, or another kernel
-// (snapshots, the adjoint, the autotuner's reference point).
-enum class SplitUse { image, fused, other };
+// the stage-wise call, the fused solve + imaging launch, snapshots, or another
+// kernel (the adjoint, the autotuner's reference point).
+enum class SplitUse { image, fused, snap, other };
+
+// Frames a workgroup images at once.
+int slots_for(const ArrayPlan& ap, SplitUse use) {
+  const int N = ap.h.nx;
+  const ImageArgs ia = engine_probe(ap);
+  if (N >= 128) return epic::cls_pair_engine(ia, N) || (epic::cls_dense_engine(ia, N) && N == 128) ? 2 : 1;
+  if (N == 64) return epic::pair_engine(ia, N) ? 8 : 4;
+  if (use == SplitUse::other || !epic::small_engine(ia, N)) return 4 * (64 / N);
+  return (use == SplitUse::fused ? epic::kSmallBodyWaves : epic::small_waves(N, epic::small_apl(N, ap.h.na))) * (64 / N);
+}
 
 // Time splits per channel for a target of `wg` workgroups, keeping >= 8 frames
 // per slot; at 64 x 64 (the two-waves-per-SIMD engines: eight waves) >= 16
@@ -727,7 +742,7 @@ int64_t splits_for_target(epic_plan_t p, const ArrayPlan& ap, int64_t T, int64_t
   const int N = ap.h.nx;
   const int64_t units = int64_t(ap.h.F) * units_for(ap);
   int64_t s = (wg + units - 1) / units;
-  const int64_t per_split = N == 64 ? 8 * 16 : 8 * int64_t(slots_for(N));
+  const int64_t per_split = N == 64 ? 8 * 16 : N >= 128 ? 8 : 8 * 4 * (64 / N);
   s = std::min<int64_t>(s, std::max<int64_t>(1, T / per_split));
   if (units * s > p->n_cu) {
     const int64_t rounds = (units * s + p->n_cu - 1) / p->n_cu;
@@ -736,29 +751,114 @@ int64_t splits_for_target(epic_plan_t p, const ArrayPlan& ap, int64_t T, int64_t
   return std::max<int64_t>(1, s);
 }
 
-int pick_splits(epic_plan_t p, const ArrayPlan& ap, int64_t T, int tuned = 0, SplitUse use = SplitUse::other) {
+// Time splits per channel from what a workgroup does: steps of `slots` frames,
+// and a set-up and reduction worth one step more in a launch of its own, three
+// (1.5 up to 32 x 32) as an item of the fused run.
+//   A launch of its own takes its rounds of workgroups over the CUs times
+//   (steps + 1): 32 x 32, 48 channels x 700: 5 splits 53 us, 4 62, 8 63, 11
+//   (the former rule's) 68; 64 x 64, 64 channels x 1000: 4 splits 221 us, 7
+//   (former) 253; 256 x 256, 2048 antennas, 64 channels x 250, with its solve:
+//   2 splits 2.05 ms, 16 (former) 2.19.
+//   The fused run's workgroups pull items one after another, those that solve
+//   from `late` steps on (their channel's solve): LWA shape 22 splits 4.66 ms,
+//   24 (former) 4.72, 16 4.77; 32 x 32, 75 channels x 1501: 16 splits 264 us, 23
+//   (former) 370.
+int splits_by_steps(epic_plan_t p, const ArrayPlan& ap, int64_t T, SplitUse use) {
+  const bool fused = use == SplitUse::fused;
   const int N = ap.h.nx;
+  const int64_t units = int64_t(ap.h.F) * units_for(ap), slots = slots_for(ap, use), most = (T + slots - 1) / slots;
+  const double setup = !fused ? 1.0 : N <= 32 ? 1.5 : 3.0;
+  // the solve of a channel in steps: about 2 us per interval and 0.25 ns per
+  // antenna sample, against 5 to 14 us per step
+  const double step_us = N <= 32 ? 5.0 : N == 64 ? 6.8 : slots == 2 ? 9.0 : 14.0;
+  const double late = (2.0 * double((T + ap.t_cal - 1) / ap.t_cal) + 0.25e-3 * double(T) * ap.h.na * ap.n_pix) / step_us;
+  const int64_t solvers = std::min<int64_t>(ap.h.F, p->n_cu - 1);
+  // at most 256 frames in one FP32 accumulator, as the former rules had on the
+  // largest shapes: rounding grows with them (HERA shape, 1000: 4.8e-7, 250: 1.4e-7)
+  const int64_t least = (most + 255) / 256;
+  int64_t best = least;
+  double cost = std::numeric_limits<double>::max();
+  auto consider = [&](int64_t s) {
+    s = std::max(least, std::min(s, most));
+    const double len = double(((T + s - 1) / s + slots - 1) / slots) + setup;
+    const int64_t items = units * s;
+    double c;
+    if (!fused) {
+      c = double((items + p->n_cu - 1) / p->n_cu) * len;
+    } else {
+      // the earliest end of an item by which all are done
+      auto done = [&](double t) {
+        return double(p->n_cu - solvers) * std::floor(t / len) + double(solvers) * std::floor(std::max(0.0, t - late) / len);
+      };
+      const double t0 = (double(items) * len + double(solvers) * std::min(late, double(items) * len)) / p->n_cu;
+      c = std::numeric_limits<double>::max();
+      for (int k = 0; k < 3; ++k) {
+        const double e1 = len * (std::floor(t0 / len) + k), e2 = late + len * (std::floor(std::max(0.0, t0 - late) / len) + k);
+        for (double e : {e1, e2})
+          if (done(e + 1e-6 * len) >= double(items)) c = std::min(c, e);
+      }
+      if (c > 1e300) c = t0 + 2 * len;
+    }
+    if (c < cost) {
+      cost = c;
+      best = s;
+    }
+  };
+  for (int64_t k = 1; k <= 24; ++k) {
+    consider(k);
+    consider(k * p->n_cu / units);                 // k rounds of workgroups
+    consider((T + k * slots - 1) / (k * slots));   // k steps each
+  }
+  return int(best);
+}
+
+// Snapshots: splits of a channel's windows, and whether the waves of a
+// workgroup share each window (few, long windows) or take whole windows each.
+// In steps of frames, as above: a shared window takes its samples over the
+// workgroup's slots and about a step and a half for its reduction, slots of
+// their own the samples of every window they hold.  (16 x 16, 309 channels of
+// two 50-sample windows: 180 us with a window per slot.)
+struct SnapPlan {
+  int splits;
+  bool group;
+};
+SnapPlan snap_plan(epic_plan_t p, const ArrayPlan& ap, int64_t T, int64_t t_acc) {
+  const int64_t n_win = (T + t_acc - 1) / t_acc, F = ap.h.F, slots = slots_for(ap, SplitUse::snap);
+  const ImageArgs ia = engine_probe(ap);
+  const bool can_group = epic::pair_engine(ia, ap.h.nx) || epic::small_engine(ia, ap.h.nx);
+  const int64_t fixed = ap.tune_splits > 0 ? ap.tune_splits : p->splits;
+  SnapPlan best{1, false};
+  double cost = std::numeric_limits<double>::max();
+  auto consider = [&](int64_t s) {
+    s = std::max<int64_t>(1, std::min(s, n_win));
+    const double rounds = double((F * s + p->n_cu - 1) / p->n_cu);
+    const double per = double((n_win + s - 1) / s), samples = double(std::min(t_acc, T));
+    const double own = rounds * (std::ceil(per / double(slots)) * samples + 1);
+    const double grp = rounds * (per * (std::ceil(samples / double(slots)) + 1.5) + 1);
+    if (own < cost) cost = own, best = SnapPlan{int(s), false};
+    if (can_group && grp < cost) cost = grp, best = SnapPlan{int(s), true};
+  };
+  if (fixed > 0) {
+    consider(fixed);
+  } else {
+    for (int64_t k = 1; k <= 12; ++k) {
+      consider(k);
+      consider(k * p->n_cu / F);
+      consider((n_win + k * slots - 1) / (k * slots));
+    }
+  }
+  return best;
+}
+
+int pick_splits(epic_plan_t p, const ArrayPlan& ap, int64_t T, int tuned = 0, SplitUse use = SplitUse::other) {
   if (tuned > 0) return int(std::max<int64_t>(1, std::min<int64_t>(tuned, std::max<int64_t>(1, T))));
   if (p->splits > 0) return int(std::max<int64_t>(1, std::min<int64_t>(p->splits, std::max<int64_t>(1, T))));
-  if (use == SplitUse::fused) {
-    // the fused run pulls items dynamically, solve workgroups joining late:
-    // half again the items of 2048 workgroups keep the last ones short, in
-    // whole rounds over the CUs (LWA shape, per fused launch: 16 splits
-    // 5.16 ms, 20: 5.07, 24: 5.02-5.07, 28: 5.14, 32: 5.17, 48: 5.18)
-    const int64_t per_split = N == 64 ? 8 * 16 : 8 * int64_t(slots_for(N));
-    const int64_t units = int64_t(ap.h.F) * units_for(ap);
-    int64_t sf = (3 * splits_for_target(p, ap, T, 2048) + 1) / 2;
-    const int64_t rounds = (units * sf + p->n_cu - 1) / p->n_cu;
-    sf = (rounds * p->n_cu + units - 1) / units;
-    return int(std::max<int64_t>(1, std::min<int64_t>(sf, std::max<int64_t>(1, T / per_split))));
+  if (use == SplitUse::image || use == SplitUse::fused) {
+    // decided once per run length (the plan's options and tables bump the generation)
+    SplitMemo& m = ap.memo[use == SplitUse::fused];
+    if (m.T != T || m.generation != p->generation) m = SplitMemo{T, p->generation, splits_by_steps(p, ap, T, use)};
+    return m.splits;
   }
-  // the separate launch of the paired 64 x 64 engine: every workgroup images
-  // the same number of frames, so two rounds over the CUs balance as well as
-  // eight and set up and reduce a quarter as often (LWA shape, per launch:
-  // 16 splits 4.38-4.44 ms, 8: 4.33, 4: 4.31-4.34, 2: 4.27-4.31; 3, one and a
-  // half rounds: 5.78); the partial images written drop from 33.6 to 8.4 MB
-  if (use == SplitUse::image && N == 64 && epic::pair_engine(engine_probe(ap), N))
-    return int(splits_for_target(p, ap, T, 2 * int64_t(p->n_cu)));
   // aim for >= 2048 workgroups (8 per CU on 256 CUs)
   return int(splits_for_target(p, ap, T, 2048));
 }
@@ -906,19 +1006,21 @@ int epic_plan_create(const epic_array_desc* arrays, int32_t n_arrays, epic_plan_
         ap.n_slots_dft = build_slots(ap.h, epic::dft_owners(ap.h.nx), ap.h.nx + 2, tab, true);
         rc = upload(&ap.d_slots_dft, reinterpret_cast<const uint2*>(tab.data()), tab.size() / 2);
       }
-      if (!rc && ap.h.nx == 64) {
+      if (!rc) {
+        const uint32_t N = uint32_t(ap.h.nx), HC = N / 2;
         std::vector<uint32_t> hi;
-        ap.n_slots_h0 = build_slots(ap.h, 64, epic::kHalfPitch, tab, false, 0);
-        ap.n_slots_h1 = build_slots(ap.h, 64, epic::kHalfPitch, hi, false, 1);
+        ap.n_slots_h0 = build_slots(ap.h, L, epic::half_pitch(ap.h.nx), tab, false, 0);
+        ap.n_slots_h1 = build_slots(ap.h, L, epic::half_pitch(ap.h.nx), hi, false, 1);
         tab.insert(tab.end(), hi.begin(), hi.end());
         rc = upload(&ap.d_slots_h, reinterpret_cast<const uint2*>(tab.data()), tab.size() / 2);
-        if (!rc && ap.h.na <= 256) {
-          std::vector<uint32_t> dg(2 * 4 * 256, 0u);
+        if (!rc && ap.h.na <= (N == 64 ? 256 : 8 * ap.h.nx)) {
+          const size_t per = N == 64 ? 4 : 8;   // antennas per lane at most
+          std::vector<uint32_t> dg(2 * 4 * per * N, 0u);
           for (int an = 0; an < ap.h.na; ++an)
             for (int k = 0; k < 4; ++k) {
               const uint32_t c = packed[size_t(an) * 4 + k], x = c & 0xffffu, y = c >> 16;
-              const size_t at = 2 * (size_t(4 * (an / 64) + k) * 64 + an % 64);
-              dg[at] = 8 * (y * epic::kHalfPitch + (x & 31)) | (x >> 5) << 16;
+              const size_t at = 2 * (size_t(4 * (an / int(N)) + k) * N + an % N);
+              dg[at] = 8 * (y * uint32_t(epic::half_pitch(ap.h.nx)) + x % HC) | (x / HC) << 16;
               std::memcpy(&dg[at + 1], &wf[size_t(an) * 4 + k], 4);
             }
           rc = upload(&ap.d_degrid, reinterpret_cast<const uint2*>(dg.data()), dg.size() / 2);
@@ -1361,16 +1463,17 @@ static bool fused_eligible(epic_plan_t plan) {
   return true;
 }
 
-// Work items {array, channel, class group, split}, most expensive first;
-// none for the arrays with their own launch.
-static int build_items(epic_plan_t plan, const std::vector<RunLayout>& lay, int64_t n_samples) {
-  std::vector<int> key{int(n_samples & 0x7fffffff), int(n_samples >> 31)};
+// Work items {array, channel, class group, split}, most expensive first (fused:
+// earliest samples first); none for the arrays with their own launch.
+static int build_items(epic_plan_t plan, const std::vector<RunLayout>& lay, int64_t n_samples, bool fused) {
+  std::vector<int> key{int(n_samples & 0x7fffffff), int(n_samples >> 31), fused ? 1 : 0};
   for (size_t i = 0; i < lay.size(); ++i) key.push_back(lay[i].splits);
   for (size_t i = 0; i < lay.size(); ++i) key.push_back(own_launch(plan, plan->arrays[i]) ? 1 : 0);
   if (plan->items_built && key == plan->items_key) return EPIC_OK;
   struct It {
     int4 w;
     double cost;
+    int64_t te;
   };
   std::vector<It> items;
   for (size_t i = 0; i < lay.size(); ++i) {
@@ -1381,10 +1484,16 @@ static int build_items(epic_plan_t plan, const std::vector<RunLayout>& lay, int6
     for (int s = 0; s < lay[i].splits; ++s) {
       const int64_t tb = n_samples * s / lay[i].splits, te = n_samples * (s + 1) / lay[i].splits;
       for (int f = 0; f < h.F; ++f)
-        for (int c = 0; c < cg; ++c) items.push_back({make_int4(int(i), f, c, s), per_frame * double(te - tb)});
+        for (int c = 0; c < cg; ++c) items.push_back({make_int4(int(i), f, c, s), per_frame * double(te - tb), te});
     }
   }
-  std::stable_sort(items.begin(), items.end(), [](const It& a, const It& b) { return a.cost > b.cost; });
+  // a fused run's items wait for the intervals of their samples, which the
+  // solve publishes in order: the earliest samples first (by cost alone, splits
+  // one sample longer than others came first, the last samples among them, and
+  // waited for the whole solve)
+  std::stable_sort(items.begin(), items.end(), [fused](const It& a, const It& b) {
+    return fused && a.te != b.te ? a.te < b.te : a.cost > b.cost;
+  });
   std::vector<int4> w(items.size());
   for (size_t k = 0; k < items.size(); ++k) w[k] = items[k].w;
   // A launch of an earlier call may still be reading the list, on any stream
@@ -1687,7 +1796,7 @@ int epic_run(epic_plan_t plan, const void* const* efield, int64_t n_samples, dou
       if (hipMalloc(&plan->d_counter, 256) != hipSuccess) return fail(EPIC_ERR_ALLOC, "counter allocation failed");
       plan->generation++;
     }
-    if ((rc = build_items(plan, lay, n_samples))) return rc;
+    if ((rc = build_items(plan, lay, n_samples, fused))) return rc;
   }
   if (fused) {
     int n_chan = 0;
@@ -1825,12 +1934,10 @@ int epic_run_snapshots(epic_plan_t plan, int32_t array, const void* efield, int6
   if ((rc = check_aligned({{efield, "efield"}, {gains, "gains"}, {images, "images"}, {gain_hist, "gain_hist"},
                            {ant_status, "ant_status"}})))
     return rc;
-  const int64_t n_win = (n_samples + t_acc - 1) / t_acc;
-  const int splits = pick_splits(plan, ap, n_samples, ap.tune_splits);
   RunLayout lay{};
   size_t need = 0;
   bool any_band = false;
-  if ((rc = layout_array(ap, n_samples, splits, 0, lay, need, any_band))) return rc;
+  if ((rc = layout_array(ap, n_samples, 1, 0, lay, need, any_band))) return rc;
   void* scr = nullptr;
   if ((rc = plan_scratch(plan, need, &scr))) return rc;
   char* sc = static_cast<char*>(scr);
@@ -1844,14 +1951,13 @@ int epic_run_snapshots(epic_plan_t plan, int32_t array, const void* efield, int6
     if (e != hipSuccess) return hip_fail(e, "calibration solve launch");
   }
   ImageArgs ia{static_cast<const uint8_t*>(efield), n_samples, h.F, h.na, h.efmt, sa.u_hist, ap.t_cal, ap.d_slots,
-               ap.n_slots, splits, nullptr, ap.d_slots_h, ap.n_slots_h0, ap.n_slots_h1};
+               ap.n_slots, 1, nullptr, ap.d_slots_h, ap.n_slots_h0, ap.n_slots_h1};
   ia.t_acc = t_acc;
   ia.snap = images;
   ia.snap_scale = 1.0 / (double(h.na_eff) * double(h.na_eff));
-  // every split holds at least one window per frame slot (per workgroup when
-  // its waves share long windows); the splits fill the chip as in epic_run
-  const bool group = t_acc >= epic::kSnapGroupWindow && epic::pair_engine(ia, h.nx);
-  ia.splits = int(std::min<int64_t>(splits, std::max<int64_t>(1, n_win / (group ? 1 : slots_for(h.nx)))));
+  const SnapPlan sp = snap_plan(plan, ap, n_samples, t_acc);
+  ia.splits = sp.splits;
+  ia.snap_group = sp.group ? 1 : 0;
   Timed tm(plan, EPIC_TIMER_IMAGE, s, true);
   hipError_t e = epic::launch_image_snap(h.nx, ia, s);
   return e == hipSuccess ? EPIC_OK : hip_fail(e, "snapshot imaging launch");

@@ -26,10 +26,10 @@ struct ImageArgs {
   int n_slots;
   int splits;               // workgroups per channel
   float* partial;           // [splits][F][N*N]
-  // schedule of the half-frame gridding (64 lanes): columns 0..31, then
-  // columns 32..63; for 64 x 64 the cell offsets are re-based to column 0 of
-  // a kHalfPitch buffer, for the residue-class engines the codes keep the
-  // sub-cell (the kernel re-bases); null when not built
+  // schedule of the half-frame gridding: columns 0..N/2-1, then N/2..N-1
+  // (N <= 64: N lanes, cell offsets re-based to column 0 of a half_pitch(N)
+  // buffer), for the residue-class engines sub-cell columns 0..31, then 32..63;
+  // null when not built
   const uint2* slots_h = nullptr;
   int n_slots_h0 = 0, n_slots_h1 = 0;
   // snapshot form: one image per window of t_acc samples, written to
@@ -38,6 +38,7 @@ struct ImageArgs {
   int64_t t_acc = 0;
   float* snap = nullptr;
   double snap_scale = 0.0;
+  int snap_group = 0;       // the waves of a workgroup share each window (two-waves-per-SIMD engines)
   // multi-class schedules of the dense residue-class engine (N = 128, 256):
   // per half of the sub-cell columns, rows of 64 x (classes per frame) sub-cell
   // owners; null when not built
@@ -65,7 +66,7 @@ struct GridArgs {
   int n_slots;
   float2* grid;             // [nt][F][N][N]
   int n_cu;
-  // half-frame schedules of the 64 x 64 grid, as in ImageArgs
+  // half-frame schedules, as in ImageArgs
   const uint2* slots_h = nullptr;
   int n_slots_h0 = 0, n_slots_h1 = 0;
 };
@@ -150,11 +151,11 @@ struct AdjointArgs {
   int k2;
   int splits;
   double2* partial;         // [splits][F][Na]
-  // half-frame schedules (64 x 64 two-waves-per-SIMD engine), as in ImageArgs
+  // half-frame schedules, as in ImageArgs
   const uint2* slots_h = nullptr;
   int n_slots_h0 = 0, n_slots_h1 = 0;
-  // degridding table of that engine, up to 256 antennas: entry (4 i + k) * 64 +
-  // lane is kernel cell k of antenna 64 i + lane: byte offset in the half frame
+  // degridding table of the half-frame engines (64 x 64: up to 256 antennas):
+  // entry (4 i + k) * N + lane is kernel cell k of antenna N i + lane: byte offset in the half frame
   // | column half << 16, weight (0 past the last antenna and for flagged ones)
   const uint2* degrid = nullptr;
 };
@@ -232,15 +233,13 @@ hipError_t launch_image_batch(const BatchImageArgs& b, int n_workgroups, hipStre
 hipError_t launch_solve_batch(const BatchSolveArgs& b, int j, int ps, hipStream_t s);
 hipError_t launch_reduce_batch(const BatchReduceArgs& b, hipStream_t s);
 
-// Snapshot windows of at least this many samples are imaged by all eight
-// waves of a paired-engine workgroup together; shorter ones by one wave each.
-constexpr int64_t kSnapGroupWindow = 64;
-
 // Half-frame buffer of the two-waves-per-SIMD engines: the 64 rows of one
 // half of the columns (32 cells each) at a pitch of 33 complex values, so
 // that 64 lanes loading their own rows stay free of bank conflicts; column 32
 // is the pad that the schedule's padding slots write.
-constexpr int kHalfPitch = 33;
+// (half_pitch(N) = N / 2 + 1 in general: 16 x 16 and 32 x 32 likewise.)
+constexpr int half_pitch(int N) { return N / 2 + 1; }
+constexpr int kHalfPitch = half_pitch(64);
 
 // Slot code of the residue-class engines' gridding schedules:
 //   8 * antenna | jx << 14 | jy << 22 | mark << 30,  and the weight (never
@@ -264,6 +263,13 @@ __host__ __device__ inline bool cls_slot_mark(uint32_t code) { return (code >> 3
 int grid_lanes(int N);
 int grid_pitch(int N);
 bool image_supported(int N, int na, int n_slots);
+// Waves of a workgroup of the 16 x 16 / 32 x 32 engine's own kernels: four per
+// SIMD at 16 x 16, three at 32 x 32 (168 registers per lane), two where the
+// staging of up to 256 antennas fills the LDS.  The persistent kernels run eight.
+constexpr int small_waves(int N, int apl) { return N == 16 ? 16 : apl == 8 ? 8 : 12; }
+constexpr int kSmallBodyWaves = 8;
+int small_apl(int N, int na);   // antennas per lane
+bool small_engine(const ImageArgs& a, int N, int waves = 0);   // the 16 x 16 / 32 x 32 engine applies (waves 0: its own launch)
 bool pair_engine(const ImageArgs& a, int N);   // the 64 x 64 two-waves-per-SIMD engine applies
 bool cls_pair_engine(const ImageArgs& a, int N);   // the 128 / 256 two-waves-per-SIMD class engine applies
 bool cls_dense_engine(const ImageArgs& a, int N);  // the dense two-waves-per-SIMD class engine applies

@@ -380,7 +380,7 @@ __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, 
   __syncthreads();
 }
 
-// Long windows (t_acc >= kSnapGroupWindow) on the paired engine: the eight
+// Few, long windows (ImageArgs::snap_group) on the paired engine: the eight
 // waves share each window's frames, as in the averaging engine, and the
 // workgroup sums them into the window's image.
 template <int APL, int FMT>

@@ -1,6 +1,7 @@
 // HIP kernels (gfx950): adjoint of fixed-gain imaging with respect to the gains.
 #include "engine.h"
 #include "image_fft.h"
+#include "image_small.h"
 
 namespace epic {
 
@@ -278,6 +279,133 @@ __global__ __launch_bounds__(kPairThreads) void k_adjoint_pair(AdjointArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same adjoint at 16 x 16 and 32 x 32, built like that imaging engine
+// (image_small.h): 64 / N frames per wave, half frames, three or four waves
+// per SIMD.  Up to four antennas per lane: with eight the compiler spilled a
+// hundred registers, and those arrays keep the one-wave form above.
+// ---------------------------------------------------------------------------
+constexpr int small_adjoint_waves(int N, int apl) { return N == 16 && apl == 2 ? 16 : 12; }
+
+template <int N, int APL, int FMT>
+__global__ __launch_bounds__(64 * small_adjoint_waves(N, APL)) void k_adjoint_small(AdjointArgs a) {
+  constexpr int W = small_adjoint_waves(N, APL), K2 = 4;
+  using G = SmallGeo<N>;
+  using L = SmallSmem<N, APL, W>;
+  constexpr int STEP = W * G::FPW;
+  static_assert(STEP * APL * N * 16 <= L::BYTES, "the partial sums' reduction fits the LDS");
+  __shared__ __align__(16) uint8_t smem[L::BYTES];
+  const int lane = threadIdx.x & 63, wave = wave_index();
+  const int h = lane / N, lam = lane % N;
+  float2* H = reinterpret_cast<float2*>(smem) + wave * L::WAVE + h * L::FRAME;
+  float2* epr = H + G::HALF;
+  uint2* stab = reinterpret_cast<uint2*>(smem + L::T_OFF);
+  const int S0 = a.n_slots_h0, S1 = a.n_slots_h1;
+  const int f = blockIdx.x % a.F, s = blockIdx.x / a.F;
+  const int64_t tb = a.n_t * s / a.splits, te = a.n_t * (s + 1) / a.splits;
+
+  load_slot_table(stab, a.slots_h, S0 + S1, N);
+  static_for<0, G::HP>([&](auto xc) { H[lam * G::HP + decltype(xc)::value] = make_float2(0.f, 0.f); });
+  __syncthreads();
+  const float2* urow = a.u + int64_t(f) * a.Na;
+  const float* Rf = a.R + int64_t(f) * N * N;
+  double2 du[APL];
+  static_for<0, APL>([&](auto ic) { du[decltype(ic)::value] = make_double2(0.0, 0.0); });
+  Raw raw[APL];
+  auto fetch_raw = [&](int64_t t0) {
+    const uint8_t* row = small_row<FMT>(a.efield, t0, te, h, f, a.F, a.Na);
+    static_for<0, APL>([&](auto ic) {
+      raw[decltype(ic)::value] = load_raw_global(row, min(lam + N * decltype(ic)::value, a.Na - 1), FMT);
+    });
+  };
+  for (int64_t t0 = tb + wave * G::FPW; t0 < te; t0 += STEP) {
+    const int lo = opaque(lam);
+    const bool active = t0 + h < te;
+    fetch_raw(t0);
+    float2 uu[APL];
+    static_for<0, APL>([&](auto ic) {
+      uu[decltype(ic)::value] = gload_at<float2>(urow, 8u * uint32_t(min(lo + N * decltype(ic)::value, a.Na - 1)));
+    });
+    static_for<0, APL>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      epr[lam + N * i] = cmul(unpack_raw(raw[i], FMT), uu[i]);
+    });
+    wave_lds_sync();
+    float2 v[N];
+    small_transform<N>(v, H, epr, stab, S0, S1, lam);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, N / 16>([&](auto cc) {
+      constexpr int c0 = 16 * decltype(cc)::value;
+      float rr[16];
+      static_for<0, 16>([&](auto kc) {
+        rr[decltype(kc)::value] = gload_at<float>(Rf + (c0 + decltype(kc)::value) * N, 4u * uint32_t(lo));
+      });
+      static_for<0, 16>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        v[c0 + k] = cscale(v[c0 + k], rr[k]);
+      });
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    fft_reg<N, -1>(v);            // conjugate transform along y: v[y], kx = lam
+    transpose_lds<N>(v, H, lam);  // lam = row y, v[kx]
+    fft_reg<N, -1>(v);            // along x: v[x] = G'(x, y = lam)
+    __builtin_amdgcn_sched_barrier(0);
+    // degrid half by half, a cell of the other half with weight zero; the
+    // samples are read again (cache resident) rather than held in registers
+    // and the table two antennas at a time: all of it would hold 8 APL registers
+    float2 gb[APL];
+    static_for<0, APL>([&](auto ic) { gb[decltype(ic)::value] = make_float2(0.f, 0.f); });
+    static_for<0, 2>([&](auto hc) {
+      constexpr int hf = decltype(hc)::value;
+      static_for<0, G::HC>([&](auto xc) {
+        H[lam * G::HP + decltype(xc)::value] = v[G::HC * hf + decltype(xc)::value];
+      });
+      wave_lds_sync();
+      static_for<0, APL / 2>([&](auto jc) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int ld = opaque(lam);
+        uint2 dg[2][K2];
+        static_for<0, 2 * K2>([&](auto kc) {
+          constexpr int i = 2 * decltype(jc)::value + decltype(kc)::value / K2, k = decltype(kc)::value % K2;
+          dg[i % 2][k] = gload_at<uint2>(a.degrid + (i * K2 + k) * N, 8u * uint32_t(ld));
+        });
+        static_for<0, 2 * K2>([&](auto kc) {
+          constexpr int i = 2 * decltype(jc)::value + decltype(kc)::value / K2, k = decltype(kc)::value % K2;
+          const float2 c = lds_at(H, dg[i % 2][k].x & 0xffffu);
+          const float w = int(dg[i % 2][k].x >> 16) == hf ? __uint_as_float(dg[i % 2][k].y) : 0.f;
+          gb[i].x = fmaf(w, c.x, gb[i].x);
+          gb[i].y = fmaf(w, c.y, gb[i].y);
+        });
+      });
+      if constexpr (hf == 1) fetch_raw(t0);
+      wave_lds_sync();
+    });
+    static_for<0, G::HC>([&](auto xc) { H[lam * G::HP + decltype(xc)::value] = make_float2(0.f, 0.f); });
+    static_for<0, APL>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      const float2 e = unpack_raw(raw[i], FMT);
+      du[i].x += double(active ? e.x * gb[i].x + e.y * gb[i].y : 0.f);
+      du[i].y += double(active ? e.x * gb[i].y - e.y * gb[i].x : 0.f);
+    });
+  }
+  // workgroup sum of the lane groups' partials (FP64) per antenna
+  __syncthreads();
+  double2* red = reinterpret_cast<double2*>(smem);   // [STEP][APL * N]
+  const int slot = wave * G::FPW + h;
+  static_for<0, APL>([&](auto ic) { red[slot * (APL * N) + lam + N * decltype(ic)::value] = du[decltype(ic)::value]; });
+  __syncthreads();
+  for (int an = threadIdx.x; an < a.Na; an += 64 * W) {
+    double2 sum = make_double2(0.0, 0.0);
+#pragma unroll 8
+    for (int q = 0; q < STEP; ++q) {
+      const double2 d = red[q * (APL * N) + an];
+      sum.x += d.x;
+      sum.y += d.y;
+    }
+    a.partial[(int64_t(s) * a.F + f) * a.Na + an] = sum;
+  }
+}
+
 // dL/dg = 2 conj(-1/g^2) scale sum_s partial  (FP64)
 __global__ __launch_bounds__(256) void k_adjoint_reduce(const double2* partial, int splits, int F, int Na,
                                                         const double2* gains, double scale, double2* out) {
@@ -318,6 +446,15 @@ struct LaunchAdjoint {
         const dim3 grid(a.F * a.splits), block(kPairThreads);
         with_format(a.fmt, [&](auto fc) {
           hipLaunchKernelGGL((k_adjoint_pair<decltype(fc)::value, APL>), grid, block, 0, s, a);
+        });
+        return hipGetLastError();
+      }
+    }
+    if constexpr (N <= 32 && APL <= 4) {
+      if (a.slots_h && a.degrid && a.n_slots_h0 + a.n_slots_h1 <= SmallSmem<N, APL, small_adjoint_waves(N, APL)>::TAB_SLOTS) {
+        with_format(a.fmt, [&](auto fc) {
+          hipLaunchKernelGGL((k_adjoint_small<N, APL, decltype(fc)::value>), dim3(a.F * a.splits),
+                             dim3(64 * small_adjoint_waves(N, APL)), 0, s, a);
         });
         return hipGetLastError();
       }

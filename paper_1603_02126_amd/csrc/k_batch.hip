@@ -55,14 +55,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_image_batch(BatchImageArgs b)
 
 int batch_body(const ImageArgs& a, int N, bool dft) {
   if (dft) return 0;
-  if (N == 16 || N == 32) {
-    const int apl = apl_for(N, a.Na);
-    const int cap = N == 16 ? (apl == 2 ? Budget<16, 2, 8>::TAB_SLOTS : apl == 4 ? Budget<16, 4, 8>::TAB_SLOTS
-                                                                                : Budget<16, 8, 8>::TAB_SLOTS)
-                            : (apl == 2 ? Budget<32, 2, 8>::TAB_SLOTS : apl == 4 ? Budget<32, 4, 8>::TAB_SLOTS : 0);
-    if (apl == 0 || a.n_slots > cap) return 0;
-    return fft8_code(N, apl);
-  }
+  if (small_engine(a, N, kSmallBodyWaves)) return small_code(N, apl_for(N, a.Na), a.fmt);
   if (N == 64) return pair_engine(a, N) ? pair_code(apl_for(N, a.Na), a.fmt) : 0;
   if (N == 128 || N == 256) {
     const int R = N / 64;

@@ -26,6 +26,7 @@
 // sample becomes independent work.
 #include "image_cls.h"
 #include "image_fft.h"
+#include "image_small.h"
 
 namespace epic {
 
@@ -36,6 +37,27 @@ template <int N, int APL>
 __global__ __launch_bounds__(256) void k_image(ImageArgs a) {
   __shared__ __align__(16) uint8_t smem[FftSmem<N, APL>::BYTES];
   image_item<N, APL>(a, blockIdx.x % a.F, blockIdx.x / a.F, smem);
+}
+
+template <int N, int APL, int FMT>
+__global__ __launch_bounds__(64 * small_waves(N, APL)) void k_image_small(ImageArgs a) {
+  constexpr int W = small_waves(N, APL);
+  __shared__ __align__(16) uint8_t smem[SmallSmem<N, APL, W>::BYTES];
+  image_item_small<N, APL, FMT, W>(a, blockIdx.x % a.F, blockIdx.x / a.F, smem);
+}
+
+template <int N, int APL, int FMT>
+__global__ __launch_bounds__(64 * small_waves(N, APL)) void k_image_small_snap(ImageArgs a) {
+  constexpr int W = small_waves(N, APL);
+  __shared__ __align__(16) uint8_t smem[SmallSmem<N, APL, W>::BYTES];
+  image_item_small_snap<N, APL, FMT, W>(a, blockIdx.x % a.F, blockIdx.x / a.F, smem);
+}
+
+template <int N, int APL, int FMT>
+__global__ __launch_bounds__(64 * small_waves(N, APL)) void k_image_small_snap_group(ImageArgs a) {
+  constexpr int W = small_waves(N, APL);
+  __shared__ __align__(16) uint8_t smem[SmallSmem<N, APL, W>::BYTES];
+  image_item_small_snap_group<N, APL, FMT, W>(a, blockIdx.x % a.F, blockIdx.x / a.F, smem);
 }
 
 template <int APL, int FMT>
@@ -144,9 +166,39 @@ bool pair_engine(const ImageArgs& a, int N) {
          a.n_slots_h0 + a.n_slots_h1 <= (apl == 2 ? PairSmem<2>::TAB_SLOTS : PairSmem<4>::TAB_SLOTS);
 }
 
+// The 16 x 16 / 32 x 32 engine: half-frame schedules that fit its LDS table
+// (any but extreme layouts, dozens of antennas on one cell).
+template <int N>
+static int small_table_slots(int apl, int waves) {
+  const bool own = waves == 0;
+  switch (apl) {
+    case 2: return own ? SmallSmem<N, 2, small_waves(N, 2)>::TAB_SLOTS : SmallSmem<N, 2, kSmallBodyWaves>::TAB_SLOTS;
+    case 4: return own ? SmallSmem<N, 4, small_waves(N, 4)>::TAB_SLOTS : SmallSmem<N, 4, kSmallBodyWaves>::TAB_SLOTS;
+    case 8: return own ? SmallSmem<N, 8, small_waves(N, 8)>::TAB_SLOTS : SmallSmem<N, 8, kSmallBodyWaves>::TAB_SLOTS;
+    default: return 0;
+  }
+}
+
+int small_apl(int N, int na) { return apl_for(N, na); }
+
+bool small_engine(const ImageArgs& a, int N, int waves) {
+  if (!(N == 16 || N == 32) || !a.slots_h) return false;
+  const int apl = apl_for(N, a.Na);
+  return a.n_slots_h0 + a.n_slots_h1 <= (N == 16 ? small_table_slots<16>(apl, waves) : small_table_slots<32>(apl, waves));
+}
+
 template <int N, int APL>
 struct LaunchImage {
   static hipError_t run(const ImageArgs& a, hipStream_t s) {
+    if constexpr (N <= 32) {
+      if (small_engine(a, N)) {
+        with_format(a.fmt, [&](auto fc) {
+          hipLaunchKernelGGL((k_image_small<N, APL, decltype(fc)::value>), dim3(a.F * a.splits),
+                             dim3(64 * small_waves(N, APL)), 0, s, a);
+        });
+        return hipGetLastError();
+      }
+    }
     if constexpr (N == 64 && (APL == 2 || APL == 4)) {
       if (pair_engine(a, N)) {
         with_format(a.fmt, [&](auto fc) {
@@ -226,12 +278,23 @@ hipError_t launch_image(int N, const ImageArgs& a, hipStream_t s) {
 template <int N, int APL>
 struct LaunchImageSnap {
   static hipError_t run(const ImageArgs& a, hipStream_t s) {
+    if constexpr (N <= 32) {
+      if (small_engine(a, N)) {
+        with_format(a.fmt, [&](auto fc) {
+          constexpr int FMT = decltype(fc)::value;
+          const dim3 grid(a.F * a.splits), block(64 * small_waves(N, APL));
+          if (a.snap_group) hipLaunchKernelGGL((k_image_small_snap_group<N, APL, FMT>), grid, block, 0, s, a);
+          else hipLaunchKernelGGL((k_image_small_snap<N, APL, FMT>), grid, block, 0, s, a);
+        });
+        return hipGetLastError();
+      }
+    }
     if constexpr (N == 64 && (APL == 2 || APL == 4)) {
       if (pair_engine(a, N)) {
         const dim3 grid(a.F * a.splits), block(kPairThreads);
         with_format(a.fmt, [&](auto fc) {
           constexpr int FMT = decltype(fc)::value;
-          if (a.t_acc >= kSnapGroupWindow) hipLaunchKernelGGL((k_image_pair_snap_group<APL, FMT>), grid, block, 0, s, a);
+          if (a.snap_group) hipLaunchKernelGGL((k_image_pair_snap_group<APL, FMT>), grid, block, 0, s, a);
           else hipLaunchKernelGGL((k_image_pair_snap<APL, FMT>), grid, block, 0, s, a);
         });
         return hipGetLastError();
