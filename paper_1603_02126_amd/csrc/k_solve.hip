@@ -19,11 +19,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_pixels(SolveArgs a) {
 }
 
 // One wave per channel: small arrays with short intervals.
+template <int FMT, bool EACH>
 __global__ __launch_bounds__(64) void k_solve_wave(SolveArgs a) {
-  __shared__ float2 ring[kSolveWaveRows * 64];
-  if (a.fmt == kCI4) solve_channel_wave<kCI4>(a, blockIdx.x, ring);
-  else if (a.fmt == kCI8) solve_channel_wave<kCI8>(a, blockIdx.x, ring);
-  else solve_channel_wave<kCF32>(a, blockIdx.x, ring);
+  solve_channel_wave_lanes<FMT, EACH>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -137,7 +135,11 @@ bool solve_by_wave(const SolveArgs& a) {
 hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
   if (!solve_supported(a.Na, a.fmt, a.n_pix)) return hipErrorInvalidValue;
   if (solve_by_wave(a)) {
-    hipLaunchKernelGGL(k_solve_wave, dim3(a.F), dim3(64), 0, s, a);
+    with_format(a.fmt, [&](auto fc) {
+      constexpr int FMT = decltype(fc)::value;
+      if (a.t_cal == 1) hipLaunchKernelGGL((k_solve_wave<FMT, true>), dim3(a.F), dim3(64), 0, s, a);
+      else hipLaunchKernelGGL((k_solve_wave<FMT, false>), dim3(a.F), dim3(64), 0, s, a);
+    });
     return hipGetLastError();
   }
   if (a.n_pix > 1) return launch_solve_pixels(a, s);
