@@ -751,6 +751,26 @@ int64_t splits_for_target(epic_plan_t p, const ArrayPlan& ap, int64_t T, int64_t
   return std::max<int64_t>(1, s);
 }
 
+// Microseconds of one channel's solve of T samples inside the fused run, from
+// the times of the solves by themselves (the several-pixel one runs there at
+// half its threads).
+double fused_solve_us(const ArrayPlan& ap, int64_t T) {
+  epic::SolveArgs a{};
+  a.n_t = T;
+  a.F = ap.h.F;
+  a.Na = ap.h.na;
+  a.fmt = ap.h.efmt;
+  a.t_cal = ap.t_cal;
+  a.n_pix = ap.n_pix;
+  const double n_int = double((T + ap.t_cal - 1) / ap.t_cal), sums = double(T) * ap.h.na;
+  if (ap.n_pix > 1) return 8.0 * n_int + 0.4e-3 * sums * ap.n_pix;
+  if (!epic::solve_by_int(a)) return 2.0 * n_int + 0.25e-3 * sums;
+  // per interval and, in blocks of 64 bytes of a sample row, per chunk of its rows
+  const int64_t blocks = (2 * ap.h.na + 63) / 64, rows = std::min<int64_t>(128, 1024 / blocks);
+  const int64_t len = std::min<int64_t>(ap.t_cal, T);
+  return n_int * (1.5 + double((len + rows - 1) / rows) * (1.2 + 0.17 * double(blocks)));
+}
+
 // Time splits per channel from what a workgroup does: steps of `slots` frames,
 // and a set-up and reduction worth one step more in a launch of its own, three
 // (1.5 up to 32 x 32) as an item of the fused run.
@@ -768,10 +788,9 @@ int splits_by_steps(epic_plan_t p, const ArrayPlan& ap, int64_t T, SplitUse use)
   const int N = ap.h.nx;
   const int64_t units = int64_t(ap.h.F) * units_for(ap), slots = slots_for(ap, use), most = (T + slots - 1) / slots;
   const double setup = !fused ? 1.0 : N <= 32 ? 1.5 : 3.0;
-  // the solve of a channel in steps: about 2 us per interval and 0.25 ns per
-  // antenna sample, against 5 to 14 us per step
+  // the solve of a channel in steps
   const double step_us = N <= 32 ? 5.0 : N == 64 ? 6.8 : slots == 2 ? 9.0 : 14.0;
-  const double late = (2.0 * double((T + ap.t_cal - 1) / ap.t_cal) + 0.25e-3 * double(T) * ap.h.na * ap.n_pix) / step_us;
+  const double late = fused_solve_us(ap, T) / step_us;
   const int64_t solvers = std::min<int64_t>(ap.h.F, p->n_cu - 1);
   // at most 256 frames in one FP32 accumulator, as the former rules had on the
   // largest shapes: rounding grows with them (HERA shape, 1000: 4.8e-7, 250: 1.4e-7)
@@ -786,18 +805,23 @@ int splits_by_steps(epic_plan_t p, const ArrayPlan& ap, int64_t T, SplitUse use)
     if (!fused) {
       c = double((items + p->n_cu - 1) / p->n_cu) * len;
     } else {
-      // the earliest end of an item by which all are done
+      // the earliest end of an item by which all are done; the first items
+      // wait for the solves to get through their samples
+      const double first = late / double(s), end = double(items) * len;
       auto done = [&](double t) {
-        return double(p->n_cu - solvers) * std::floor(t / len) + double(solvers) * std::floor(std::max(0.0, t - late) / len);
+        return double(p->n_cu - solvers) * std::floor(std::max(0.0, t - first) / len) +
+               double(solvers) * std::floor(std::max(0.0, t - late) / len);
       };
-      const double t0 = (double(items) * len + double(solvers) * std::min(late, double(items) * len)) / p->n_cu;
+      const double t0 = (end + double(solvers) * std::min(late, end) + double(p->n_cu - solvers) * std::min(first, end)) / p->n_cu;
       c = std::numeric_limits<double>::max();
       for (int k = 0; k < 3; ++k) {
-        const double e1 = len * (std::floor(t0 / len) + k), e2 = late + len * (std::floor(std::max(0.0, t0 - late) / len) + k);
+        const double e1 = first + len * (std::floor(std::max(0.0, t0 - first) / len) + k),
+                     e2 = late + len * (std::floor(std::max(0.0, t0 - late) / len) + k);
         for (double e : {e1, e2})
           if (done(e + 1e-6 * len) >= double(items)) c = std::min(c, e);
       }
       if (c > 1e300) c = t0 + 2 * len;
+      c = std::max(c, late + len);   // a channel's last item waits for its last interval
     }
     if (c < cost) {
       cost = c;
@@ -1618,8 +1642,9 @@ static int enqueue_fused(epic_plan_t plan, const std::vector<RunLayout>& lay, ch
                           ap.t_cal, reinterpret_cast<float*>(scr + lay[i].p_off), lay[i].splits);
     b.code[i] = body_of(plan, ap);
     const epic::SolveArgs& a = sa[i];
-    const int code = ap.n_pix > 1 ? epic::kFusedMultiCode + solve_ps(ap.h)
-                                  : 100 * epic::solve_main_j(ap.h.na) + solve_ps(ap.h);
+    const int code = ap.n_pix > 1         ? epic::kFusedMultiCode + solve_ps(ap.h)
+                     : epic::solve_by_int(a) ? epic::kSolveIntCode + epic::solve_main_j(ap.h.na)
+                                             : 100 * epic::solve_main_j(ap.h.na) + solve_ps(ap.h);
     fa.sx[i] = epic::FusedSolveExtra{a.A, a.D, a.hold, a.gains, a.g_hist, a.status, a.na_eff, a.gamma, a.n_int,
                                      code, ap.n_pix};
     fa.chan_off[i + 1] = fa.chan_off[i] + ap.h.F;
@@ -1653,6 +1678,7 @@ static int enqueue_run(epic_plan_t plan, const std::vector<RunLayout>& lay, char
   // FP32 u of every interval from the gain history the solve wrote
   auto hist_to_u = [&](int i) -> hipError_t {
     const HostArray& h = plan->arrays[i].h;
+    if (plan->arrays[i].band_mode == EPIC_BAND_NONE && epic::solve_writes_u(sa[i])) return hipSuccess;
     return epic::launch_hist_to_u(sa[i].g_hist, plan->arrays[i].d_hold, lay[i].n_int, h.F, h.na, sa[i].u_hist, s);
   };
   if (fused) return enqueue_fused(plan, lay, scr, sa, efield, n_samples, image, s, timed);
@@ -1947,7 +1973,8 @@ int epic_run_snapshots(epic_plan_t plan, int32_t array, const void* efield, int6
   {
     Timed tm(plan, EPIC_TIMER_SOLVE, s, true);
     hipError_t e = solve_array(plan, ap, sa, sc + lay.band_off, s);
-    if (e == hipSuccess) e = epic::launch_hist_to_u(sa.g_hist, ap.d_hold, lay.n_int, h.F, h.na, sa.u_hist, s);
+    if (e == hipSuccess && !(ap.band_mode == EPIC_BAND_NONE && epic::solve_writes_u(sa)))
+      e = epic::launch_hist_to_u(sa.g_hist, ap.d_hold, lay.n_int, h.F, h.na, sa.u_hist, s);
     if (e != hipSuccess) return hip_fail(e, "calibration solve launch");
   }
   ImageArgs ia{static_cast<const uint8_t*>(efield), n_samples, h.F, h.na, h.efmt, sa.u_hist, ap.t_cal, ap.d_slots,

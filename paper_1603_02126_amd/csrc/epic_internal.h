@@ -97,7 +97,7 @@ struct SolveArgs {
   const uint8_t* hold;      // [F][Na] kHold* bits
   double na_eff, gamma;
   double2* gains;           // [F][Na] in/out
-  float2* u_hist;           // [n_int][F][Na] (written by launch_hist_to_u from g_hist)
+  float2* u_hist;           // [n_int][F][Na] (by the solve, or by launch_hist_to_u from g_hist)
   double2* g_hist;          // [n_int+1][F][Na], required
   uint32_t* status;         // [F][Na] or null
   int n_pix = 1;            // tapped pixels (1..kMaxPix; > 1 needs Na <= kSolveThreads)
@@ -211,6 +211,7 @@ struct FusedSolveExtra {
   int n_pix;                // tapped pixels
 };
 constexpr int kFusedMultiCode = 1000;
+constexpr int kSolveIntCode = 2000;   // + J: the matrix-core solve of integer samples
 
 struct FusedArgs {
   FusedSolveExtra sx[kMaxBatch];
@@ -303,6 +304,10 @@ hipError_t launch_solve(const SolveArgs& a, hipStream_t s);
 // The solve of these arrays runs one wave per channel (small arrays, short
 // intervals): launch_solve picks it, so a batched solve leaves them to it.
 bool solve_by_wave(const SolveArgs& a);
+// integer samples and up to 1024 antennas: the matrix-core solve (solve_int.h)
+bool solve_by_int(const SolveArgs& a);
+// the solve writes u_hist itself (no launch_hist_to_u)
+bool solve_writes_u(const SolveArgs& a);
 bool band_supported(int na, int fmt);
 // cooperative launch; *groups receives the number of workgroups
 hipError_t launch_solve_band(const BandArgs& b, int n_cu, hipStream_t s, int* groups = nullptr);

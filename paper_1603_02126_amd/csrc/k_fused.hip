@@ -1,7 +1,7 @@
 // HIP kernels (gfx950): the fused run, one launch for the EPICal
 // calibration solve and the imaging of every array of a plan.
 #include "batch_bodies.h"
-#include "solve.h"
+#include "solve_int.h"
 
 namespace epic {
 
@@ -43,6 +43,14 @@ __device__ __noinline__ void fused_solve_call(const SolveArgs& a, int f, uint8_t
   else solve_channel_fmt<J, PS, kCF32, kSolveMainThreads, true>(la, f, smem, progress);
 }
 
+static_assert(SolveIntSmem::BYTES <= kLdsBytes, "the matrix-core solve runs in the fused kernel's LDS");
+template <int J>
+__device__ __noinline__ void fused_int_call(const SolveArgs& a, int f, uint8_t* smem, int* progress) {
+  const SolveArgs la = uniform_copy(a);
+  f = __builtin_amdgcn_readfirstlane(f);
+  solve_channel_int_fmt<J, true>(la, f, smem, progress);
+}
+
 // Several tapped pixels (arrays of at most kSolveMainThreads antennas).
 template <int PS>
 __device__ __noinline__ void fused_multi_call(const SolveArgs& a, int f, uint8_t* smem, int* progress) {
@@ -58,6 +66,8 @@ __device__ __forceinline__ void run_solve(int code, const SolveArgs& a, int f, u
     case kFusedMultiCode + 16: fused_multi_call<16>(a, f, smem, progress); break;
     case kFusedMultiCode + 4: fused_multi_call<4>(a, f, smem, progress); break;
     case kFusedMultiCode + 1: fused_multi_call<1>(a, f, smem, progress); break;
+    case kSolveIntCode + 1: fused_int_call<1>(a, f, smem, progress); break;
+    case kSolveIntCode + 2: fused_int_call<2>(a, f, smem, progress); break;
     case 116: fused_solve_call<1, 16>(a, f, smem, progress); break;
     case 104: fused_solve_call<1, 4>(a, f, smem, progress); break;
     case 101: fused_solve_call<1, 1>(a, f, smem, progress); break;
