@@ -262,7 +262,9 @@ int epical_set_denominator(epic_plan_t plan, int32_t array, const double* D);
  *                        the persistent kernel, the FFT transform) and the
  *                        plan's channels number fewer than the GPU's CUs (the
  *                        solve, one workgroup per channel, leaves CUs idle),
- *                        epic_run makes one launch for the calibration solve
+ *                        unless one array's solve is too short against its
+ *                        imaging to be worth it (one tapped pixel, up to 64 x
+ *                        64), epic_run makes one launch for the calibration solve
  *                        and the imaging: the solve of each channel publishes
  *                        each interval's calibration as soon as it is known and
  *                        the imaging of a time split starts once its intervals

@@ -764,7 +764,7 @@ double fused_solve_us(const ArrayPlan& ap, int64_t T) {
   a.n_pix = ap.n_pix;
   const double n_int = double((T + ap.t_cal - 1) / ap.t_cal), sums = double(T) * ap.h.na;
   if (ap.n_pix > 1) return 8.0 * n_int + 0.4e-3 * sums * ap.n_pix;
-  if (!epic::solve_by_int(a)) return 2.0 * n_int + 0.25e-3 * sums;
+  if (!epic::solve_by_int(a)) return 2.2 * n_int + std::max(0.05 * double(T), ap.h.na > 256 ? 0.5e-3 * sums : 0.0);
   // per interval and, in blocks of 64 bytes of a sample row, per chunk of its rows
   const int64_t blocks = (2 * ap.h.na + 63) / 64, rows = std::min<int64_t>(128, 1024 / blocks);
   const int64_t len = std::min<int64_t>(ap.t_cal, T);
@@ -823,6 +823,9 @@ int splits_by_steps(epic_plan_t p, const ArrayPlan& ap, int64_t T, SplitUse use)
       if (c > 1e300) c = t0 + 2 * len;
       c = std::max(c, late + len);   // a channel's last item waits for its last interval
     }
+    // the partial images' reduction: a launch whose threads read them one after
+    // another, eight at a time, at 5 TB/s at best
+    c += double(s) * (0.04 + double(ap.h.F) * N * N * 4.0 / 5e6) / step_us;
     if (c < cost) {
       cost = c;
       best = s;
@@ -1487,6 +1490,24 @@ static bool fused_eligible(epic_plan_t plan) {
   return true;
 }
 
+// Whether a run of one array with one tapped pixel is faster as one launch.
+// That hides the solve, but images at two waves per SIMD up to 32 x 32, where a
+// launch of its own has four, and pays for its items' set-up.  Measured, us, one
+// launch against two (solve, imaging of the two):
+//   16 x 16:  85 / 70 (39, 24),  380 / 330 (99, 224)
+//   32 x 32: 127 / 112 (39, 67), 345 / 320 (65, 248), 117 / 125 (62, 57),
+//            218 / 239 (88, 150)
+//   64 x 64: 310 / 298 (65, 220), 560 / 506 (88, 410), 539 / 484 (78, 400),
+//            359 / 481 (312, 160), 4467 / 4582 (430, 4130)
+// The lines are fits to these; 128 x 128 and 256 x 256 differ by less than 1 %.
+static bool fused_pays(const ArrayPlan& ap, int64_t T) {
+  const double frames = double(ap.h.F) * double(T), solve = fused_solve_us(ap, T);
+  if (ap.h.nx <= 16) return solve > 42.0 + 0.47 * 0.37e-3 * frames;
+  if (ap.h.nx <= 32) return solve > 42.0 + 0.18 * 1.24e-3 * frames;
+  if (ap.h.nx <= 64) return solve > 88.0 + 0.03 * 3.2e-3 * frames;
+  return true;
+}
+
 // Work items {array, channel, class group, split}, most expensive first (fused:
 // earliest samples first); none for the arrays with their own launch.
 static int build_items(epic_plan_t plan, const std::vector<RunLayout>& lay, int64_t n_samples, bool fused) {
@@ -1697,26 +1718,40 @@ static int enqueue_run(epic_plan_t plan, const std::vector<RunLayout>& lay, char
     }
     return EPIC_OK;
   }
-  // calibration: one launch when every array shares the solve variant
+  // calibration: one launch for the arrays of the matrix-core solve (those with
+  // the most antennas, whose channels take longest, first: a call of eight
+  // uneven arrays 6.84 ms with launches one after another, 6.32 so), and one for
+  // the others if they share the solve variant
   {
     Timed tm(plan, EPIC_TIMER_SOLVE, s, timed);
-    bool same = true;
-    const int j0 = epic::solve_main_j(plan->arrays[0].h.na), ps0 = solve_ps(plan->arrays[0].h);
-    for (int i = 1; i < na_arr; ++i)
-      same = same && epic::solve_main_j(plan->arrays[i].h.na) == j0 && solve_ps(plan->arrays[i].h) == ps0;
-    for (int i = 0; i < na_arr; ++i) same = same && !epic::solve_by_wave(sa[i]) && sa[i].n_pix == 1;
-    if (same) {
+    std::vector<int> ints, rest;
+    for (int i = 0; i < na_arr; ++i) (epic::solve_by_int(sa[i]) ? ints : rest).push_back(i);
+    std::stable_sort(ints.begin(), ints.end(), [&](int x, int y) { return sa[x].Na > sa[y].Na; });
+    auto together = [&](const std::vector<int>& list) {
       epic::BatchSolveArgs b{};
-      b.n_arrays = na_arr;
+      b.n_arrays = int(list.size());
       b.chan_off[0] = 0;
-      for (int i = 0; i < na_arr; ++i) {
-        b.arr[i] = sa[i];
-        b.chan_off[i + 1] = b.chan_off[i] + plan->arrays[i].h.F;
+      for (int k = 0; k < b.n_arrays; ++k) {
+        b.arr[k] = sa[list[k]];
+        b.chan_off[k + 1] = b.chan_off[k] + plan->arrays[list[k]].h.F;
       }
-      hipError_t e = epic::launch_solve_batch(b, j0, ps0, s);
+      return b;
+    };
+    if (!ints.empty()) {
+      hipError_t e = ints.size() > 1 ? epic::launch_solve_int_batch(together(ints), s) : epic::launch_solve(sa[ints[0]], s);
+      if (e != hipSuccess) return hip_fail(e, "calibration solve launch");
+    }
+    bool same = !rest.empty();
+    for (int i : rest)
+      same = same && epic::solve_main_j(plan->arrays[i].h.na) == epic::solve_main_j(plan->arrays[rest[0]].h.na) &&
+             solve_ps(plan->arrays[i].h) == solve_ps(plan->arrays[rest[0]].h) && !epic::solve_by_wave(sa[i]) &&
+             sa[i].n_pix == 1;
+    if (same) {
+      const HostArray& h = plan->arrays[rest[0]].h;
+      hipError_t e = epic::launch_solve_batch(together(rest), epic::solve_main_j(h.na), solve_ps(h), s);
       if (e != hipSuccess) return hip_fail(e, "batched calibration solve launch");
     } else {
-      for (int i = 0; i < na_arr; ++i) {
+      for (int i : rest) {
         hipError_t e = epic::launch_solve(sa[i], s);
         if (e != hipSuccess) return hip_fail(e, "calibration solve launch");
       }
@@ -1799,14 +1834,17 @@ int epic_run(epic_plan_t plan, const void* const* efield, int64_t n_samples, dou
   std::vector<RunLayout> lay;
   size_t need = 0;
   bool all_batchable = false, any_band = false;
-  const bool fused_plan = plan && plan->arrays.size() <= size_t(epic::kMaxBatch) && fused_eligible(plan);
+  const bool eligible = plan && plan->arrays.size() <= size_t(epic::kMaxBatch) && fused_eligible(plan);
+  // (a captured run of one array is the one launch wherever that is possible)
+  const bool fused_plan = eligible && (plan->graph || plan->arrays.size() > 1 || plan->arrays[0].n_pix > 1 ||
+                                       fused_pays(plan->arrays[0], std::max<int64_t>(n_samples, 1)));
   int rc = prepare_run(plan, efield, n_samples, gains, image, gain_hist, ant_status, lay, need, all_batchable,
                        any_band, nullptr, fused_plan);
   if (rc) return rc;
   const int na_arr = int(plan->arrays.size());
   if (any_band && plan->batch == 1)
     return fail(EPIC_ERR_UNSUPPORTED, "gains shared over a band run in the per-array form (EPIC_OPT_BATCH 0 or 2)");
-  const bool fused = !any_band && all_batchable && fused_eligible(plan);
+  const bool fused = !any_band && all_batchable && fused_plan;
   const bool batched = !any_band && all_batchable && (plan->batch == 1 || (plan->batch == 0 && na_arr > 1));
   // a graph needs the batched form or a fused run; a single array of float
   // samples at 64 x 64 and above was never captured without EPIC_OPT_BATCH = 1

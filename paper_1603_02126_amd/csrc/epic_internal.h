@@ -231,6 +231,7 @@ constexpr int kFusedWaitPolls = 1 << 23;
 // array is imaged by its own launch in the batched sequence).
 int batch_body(const ImageArgs& a, int N, bool dft);
 hipError_t launch_image_batch(const BatchImageArgs& b, int n_workgroups, hipStream_t s);
+hipError_t launch_solve_int_batch(const BatchSolveArgs& b, hipStream_t s);   // arrays of solve_by_int
 hipError_t launch_solve_batch(const BatchSolveArgs& b, int j, int ps, hipStream_t s);
 hipError_t launch_reduce_batch(const BatchReduceArgs& b, hipStream_t s);
 

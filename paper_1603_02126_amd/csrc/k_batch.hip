@@ -78,9 +78,9 @@ __global__ __launch_bounds__(256) void k_reduce_batch(BatchReduceArgs b) {
   if (g >= b.off[b.n_arrays]) return;
   int i = 0;
   while (i + 1 < b.n_arrays && g >= b.off[i + 1]) ++i;
+  i = __builtin_amdgcn_readfirstlane(i);   // whole images: the same for the workgroup's 256 pixels
   const int64_t j = g - b.off[i];
-  double s = 0.0;
-  for (int k = 0; k < b.splits[i]; ++k) s += double(b.partial[i][int64_t(k) * b.per_split[i] + j]);
+  const double s = partial_sum(b.partial[i] + j, b.splits[i], b.per_split[i]);
   b.image[i][j] = b.error && *b.error ? __builtin_nanf("") : float(s * b.scale[i]);
 }
 

@@ -119,9 +119,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* partial, int splits
                                                 double scale, float* image) {
   const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (i >= per_split) return;
-  double s = 0.0;
-  for (int k = 0; k < splits; ++k) s += double(partial[int64_t(k) * per_split + i]);
-  image[i] = float(s * scale);
+  image[i] = float(partial_sum(partial + i, splits, per_split) * scale);
 }
 
 // ---------------------------------------------------------------------------

@@ -152,6 +152,22 @@ bool solve_by_int(const SolveArgs& a) {
 
 bool solve_writes_u(const SolveArgs& a) { return solve_by_int(a); }
 
+// Channels of several arrays: the variant by the workgroup's array.
+__global__ __launch_bounds__(kSolveMainThreads) void k_solve_int_batch(BatchSolveArgs b) {
+  __shared__ __align__(16) uint8_t smem[SolveIntSmem::BYTES];
+  int i = 0;
+  while (i + 1 < b.n_arrays && int(blockIdx.x) >= b.chan_off[i + 1]) ++i;
+  const SolveArgs& a = b.arr[i];
+  const int f = int(blockIdx.x) - b.chan_off[i];
+  if (a.Na <= kSolveMainThreads) solve_channel_int_fmt<1, false>(a, f, smem);
+  else solve_channel_int_fmt<2, false>(a, f, smem);
+}
+
+hipError_t launch_solve_int_batch(const BatchSolveArgs& b, hipStream_t s) {
+  hipLaunchKernelGGL(k_solve_int_batch, dim3(b.chan_off[b.n_arrays]), dim3(kSolveMainThreads), 0, s, b);
+  return hipGetLastError();
+}
+
 hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
   if (!solve_supported(a.Na, a.fmt, a.n_pix)) return hipErrorInvalidValue;
   if (solve_by_wave(a)) {

@@ -37,3 +37,33 @@ def test_int_solve_matches_oracle(cuda, overlap, n, na, efmt, n_samples, t_cal, 
     assert gain_err(got["hist"], ref["gains"]) <= GAIN_RTOL
     assert image_err(got["image"], ref["image"]).max() <= IMAGE_RTOL
     assert ((got["status"] & 1) == (wl.array.flags() != 0)).all()
+
+
+@pytest.mark.parametrize("arrays", [
+    [(32, 100, synth.FMT_CI8), (32, 90, synth.FMT_CI8)],                                # one variant of the FP64 solve
+    [(128, 600, synth.FMT_CI4), (32, 33, synth.FMT_CF32), (64, 255, synth.FMT_CI8)],    # one and two antennas per thread
+])
+def test_batched_int_solve_equals_the_arrays_own(cuda, arrays):
+    """Several arrays' channels in one launch: the gains of the arrays run by
+    themselves bit for bit, the images within rounding."""
+    import torch
+    from paper_1603_02126_amd import lib
+    wls = [synth.config_small(seed=7 + i, n=n, efmt=efmt, n_ant=na, n_chan=3, n_samples=70, t_cal=30)
+           for i, (n, na, efmt) in enumerate(arrays)]
+    es = [torch.from_numpy(np.ascontiguousarray(synth.make_efield(w))).to(cuda) for w in wls]
+
+    def run(which):
+        with lib.Plan([wls[i].array for i in which]) as plan:
+            plan.set_option(lib.OPT_OVERLAP, 0)
+            for k, i in enumerate(which):
+                plan.set_model(k, wls[i].model_lmS, wls[i].cal_lm, wls[i].gamma, wls[i].t_cal)
+            gs = [torch.from_numpy(np.ascontiguousarray(wls[i].g0)).to(cuda) for i in which]
+            imgs = [torch.zeros((3, wls[i].array.ny, wls[i].array.nx), dtype=torch.float32, device=cuda) for i in which]
+            plan.run([es[i] for i in which], 70, gs, imgs)
+            torch.cuda.synchronize()
+            return [g.cpu().numpy() for g in gs], [im.cpu().numpy() for im in imgs]
+    gs, imgs = run(range(len(wls)))
+    for i in range(len(wls)):
+        (g1,), (im1,) = run([i])
+        np.testing.assert_array_equal(gs[i], g1)
+        assert image_err(imgs[i], im1).max() <= IMAGE_RTOL
