@@ -17,6 +17,8 @@
 // rounded once (and its factors to 2^-62 of the largest) where an FP64 sum
 // rounds at every term.  What remains per interval is latency: five barriers,
 // the digits and the update.
+// Largest error of P over the largest |P| against exact sums: 16 antennas 6.5e-17
+// (FP64 sums 1.5e-16), 256 6.6e-17 (3.3e-16), 900 8.6e-17 (4.6e-16).
 // 64 channels, 50 intervals, per interval, FP64 FMAs (four per sample in each
 // contraction, after two conversions) against this:
 //   intervals of 100: 256 antennas ci4 7.6 -> 4.4 us, 255 ci8 (rows of no
