@@ -302,6 +302,7 @@ bool solve_supported(int na, int fmt, int n_pix = 1);
 bool solve_multi_fusable(int na, int fmt);
 int solve_main_j(int na);   // antennas per thread slot of the single-pixel solve
 hipError_t launch_solve(const SolveArgs& a, hipStream_t s);
+hipError_t launch_solve_int(const SolveArgs& a, hipStream_t s);   // arrays of solve_by_int
 // The solve of these arrays runs one wave per channel (small arrays, short
 // intervals): launch_solve picks it, so a batched solve leaves them to it.
 bool solve_by_wave(const SolveArgs& a);

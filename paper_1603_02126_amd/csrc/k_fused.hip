@@ -20,35 +20,25 @@ static_assert(kSolveMainThreads == kBatchThreads, "solve tasks run on the imagin
 static_assert(SolveSmem::BYTES <= kLdsBytes, "the solve fits the shared LDS arena");
 static_assert(sizeof(BatchImageArgs) + sizeof(FusedArgs) <= 4096, "kernel arguments of the fused run");
 
-template <typename T>
-__device__ __forceinline__ T uniform_copy(const T& a) {
-  static_assert(sizeof(T) % 4 == 0, "word-wise copy");
-  T r;
-  uint32_t words[sizeof(T) / 4];
-  __builtin_memcpy(words, &a, sizeof(T));
-  static_for<0, int(sizeof(T) / 4)>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    words[i] = __builtin_amdgcn_readfirstlane(words[i]);
-  });
-  __builtin_memcpy(&r, words, sizeof(T));
-  return r;
-}
-
 template <int J, int PS>
-__device__ __noinline__ void fused_solve_call(const SolveArgs& a, int f, uint8_t* smem, int* progress) {
+__device__ __noinline__ void fused_solve_call(const SolveArgs& a, int f, uint8_t* smem, int* progress, int n0 = 0,
+                                              bool u_done = false) {
   const SolveArgs la = uniform_copy(a);
   f = __builtin_amdgcn_readfirstlane(f);
-  if (la.fmt == kCI4) solve_channel_fmt<J, PS, kCI4, kSolveMainThreads, true>(la, f, smem, progress);
-  else if (la.fmt == kCI8) solve_channel_fmt<J, PS, kCI8, kSolveMainThreads, true>(la, f, smem, progress);
-  else solve_channel_fmt<J, PS, kCF32, kSolveMainThreads, true>(la, f, smem, progress);
+  n0 = __builtin_amdgcn_readfirstlane(n0);
+  u_done = __builtin_amdgcn_readfirstlane(u_done);
+  if (la.fmt == kCI4) solve_channel_fmt<J, PS, kCI4, kSolveMainThreads, true>(la, f, smem, progress, n0, u_done);
+  else if (la.fmt == kCI8) solve_channel_fmt<J, PS, kCI8, kSolveMainThreads, true>(la, f, smem, progress, n0, u_done);
+  else solve_channel_fmt<J, PS, kCF32, kSolveMainThreads, true>(la, f, smem, progress, n0, u_done);
 }
 
 static_assert(SolveIntSmem::BYTES <= kLdsBytes, "the matrix-core solve runs in the fused kernel's LDS");
 template <int J>
-__device__ __noinline__ void fused_int_call(const SolveArgs& a, int f, uint8_t* smem, int* progress) {
+__device__ __noinline__ int fused_int_call(const SolveArgs& a, int f, uint8_t* smem, int* progress) {
   const SolveArgs la = uniform_copy(a);
   f = __builtin_amdgcn_readfirstlane(f);
-  solve_channel_int_fmt<J, true>(la, f, smem, progress);
+  return la.fmt == kCI4 ? solve_channel_int<kCI4, J, true>(la, f, smem, progress)
+                        : solve_channel_int<kCI8, J, true>(la, f, smem, progress);
 }
 
 // Several tapped pixels (arrays of at most kSolveMainThreads antennas).
@@ -61,24 +51,28 @@ __device__ __noinline__ void fused_multi_call(const SolveArgs& a, int f, uint8_t
   else solve_channel_multi<PS, kCF32, kSolveMainThreads, true>(la, f, smem, progress);
 }
 
-__device__ __forceinline__ void run_solve(int code, const SolveArgs& a, int f, uint8_t* smem, int* progress) {
+// The solve of channel f by the array's variant; n0 intervals are published (and
+// u_done, as in solve_channel_fmt).  Returns the intervals solved.
+__device__ __forceinline__ int run_solve(int code, const SolveArgs& a, int f, uint8_t* smem, int* progress, int n0 = 0,
+                                         bool u_done = false) {
   switch (code) {
     case kFusedMultiCode + 16: fused_multi_call<16>(a, f, smem, progress); break;
     case kFusedMultiCode + 4: fused_multi_call<4>(a, f, smem, progress); break;
     case kFusedMultiCode + 1: fused_multi_call<1>(a, f, smem, progress); break;
-    case kSolveIntCode + 1: fused_int_call<1>(a, f, smem, progress); break;
-    case kSolveIntCode + 2: fused_int_call<2>(a, f, smem, progress); break;
-    case 116: fused_solve_call<1, 16>(a, f, smem, progress); break;
-    case 104: fused_solve_call<1, 4>(a, f, smem, progress); break;
-    case 101: fused_solve_call<1, 1>(a, f, smem, progress); break;
-    case 216: fused_solve_call<2, 16>(a, f, smem, progress); break;
-    case 204: fused_solve_call<2, 4>(a, f, smem, progress); break;
-    case 201: fused_solve_call<2, 1>(a, f, smem, progress); break;
-    case 416: fused_solve_call<4, 16>(a, f, smem, progress); break;
-    case 404: fused_solve_call<4, 4>(a, f, smem, progress); break;
-    case 401: fused_solve_call<4, 1>(a, f, smem, progress); break;
+    case kSolveIntCode + 1: return fused_int_call<1>(a, f, smem, progress);
+    case kSolveIntCode + 2: return fused_int_call<2>(a, f, smem, progress);
+    case 116: fused_solve_call<1, 16>(a, f, smem, progress, n0, u_done); break;
+    case 104: fused_solve_call<1, 4>(a, f, smem, progress, n0, u_done); break;
+    case 101: fused_solve_call<1, 1>(a, f, smem, progress, n0, u_done); break;
+    case 216: fused_solve_call<2, 16>(a, f, smem, progress, n0, u_done); break;
+    case 204: fused_solve_call<2, 4>(a, f, smem, progress, n0, u_done); break;
+    case 201: fused_solve_call<2, 1>(a, f, smem, progress, n0, u_done); break;
+    case 416: fused_solve_call<4, 16>(a, f, smem, progress, n0, u_done); break;
+    case 404: fused_solve_call<4, 4>(a, f, smem, progress, n0, u_done); break;
+    case 401: fused_solve_call<4, 1>(a, f, smem, progress, n0, u_done); break;
     default: break;
   }
+  return a.n_int;
 }
 
 __global__ void k_fused_reset(int* ticket, int* counter, int* error, int* progress, int n) {
@@ -128,8 +122,20 @@ __global__ __launch_bounds__(kBatchThreads) void k_run_fused(BatchImageArgs b, F
     }
     __syncthreads();
     if (t >= fa.n_solve) break;   // every wave of the workgroup leaves together
-    run_solve(fa.sx[i].code, *reinterpret_cast<const SolveArgs*>(item_raw), t - fa.chan_off[i], smem,
-              fa.progress + fa.chan_off[i]);
+    SolveArgs& sa = *reinterpret_cast<SolveArgs*>(item_raw);
+    int* progress = fa.progress + fa.chan_off[i];
+    int code = fa.sx[i].code;
+    for (int n0 = 0;;) {
+      const bool rest = code < kFusedMultiCode && fa.sx[i].code > kSolveIntCode;
+      n0 += __builtin_amdgcn_readfirstlane(run_solve(code, sa, t - fa.chan_off[i], smem, progress, n0, rest));
+      if (n0 >= fa.sx[i].n_int) break;
+      // the matrix-core solve left the rest to the FP64 one
+      __syncthreads();
+      if (threadIdx.x == 0) sa = from_interval(sa, n0);
+      __syncthreads();
+      const int row = sa.Na * efmt_bytes(sa.fmt);
+      code = 100 * (code - kSolveIntCode) + (row % 16 == 0 ? 16 : row % 4 == 0 ? 4 : 1);
+    }
     __syncthreads();              // item_l and item_raw are rewritten next
   }
   // imaging items

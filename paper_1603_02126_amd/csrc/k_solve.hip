@@ -3,7 +3,6 @@
 
 #include "solve.h"
 #include "solve_band.h"
-#include "solve_int.h"
 
 namespace epic {
 
@@ -11,12 +10,6 @@ template <int J, int PS>
 __global__ __launch_bounds__(kSolveMainThreads) void k_solve(SolveArgs a) {
   __shared__ __align__(16) uint8_t smem[SolveSmem::BYTES];
   solve_channel<J, PS>(a, blockIdx.x, smem);
-}
-
-template <int FMT, int J>
-__global__ __launch_bounds__(kSolveMainThreads) void k_solve_int(SolveArgs a) {
-  __shared__ __align__(16) uint8_t smem[SolveIntSmem::BYTES];
-  solve_channel_int<FMT, J, false>(a, blockIdx.x, smem);
 }
 
 template <int PS>
@@ -139,35 +132,6 @@ bool solve_by_wave(const SolveArgs& a) {
   return a.Na <= kSolveWaveMaxAnt && a.n_pix == 1 && a.t_cal <= kSolveWaveMaxTcal;
 }
 
-// Integer samples, one tapped pixel, up to 1024 antennas (its LDS) and rows of
-// at least one 16-byte piece, a chunk's rows within 32-bit offsets: the
-// matrix-core solve.  Its steps per interval cost the same few microseconds
-// however short the interval: 256 antennas of ci4, us per interval, FP64 FMAs
-// against it, 2.4 / 3.2 at 8 samples, 3.5 / 3.3 at 25, 7.6 / 4.4 at 100.
-bool solve_by_int(const SolveArgs& a) {
-  const int64_t RB = int64_t(a.Na) * efmt_bytes(a.fmt);
-  return std::min(a.t_cal, a.n_t) >= kSolveIntMinSamples && a.fmt != kCF32 && a.Na <= kSolveIntMaxAnt && RB >= 16 && a.F * RB < (int64_t(1) << 24) && a.n_pix == 1 &&
-         !solve_by_wave(a);
-}
-
-bool solve_writes_u(const SolveArgs& a) { return solve_by_int(a); }
-
-// Channels of several arrays: the variant by the workgroup's array.
-__global__ __launch_bounds__(kSolveMainThreads) void k_solve_int_batch(BatchSolveArgs b) {
-  __shared__ __align__(16) uint8_t smem[SolveIntSmem::BYTES];
-  int i = 0;
-  while (i + 1 < b.n_arrays && int(blockIdx.x) >= b.chan_off[i + 1]) ++i;
-  const SolveArgs& a = b.arr[i];
-  const int f = int(blockIdx.x) - b.chan_off[i];
-  if (a.Na <= kSolveMainThreads) solve_channel_int_fmt<1, false>(a, f, smem);
-  else solve_channel_int_fmt<2, false>(a, f, smem);
-}
-
-hipError_t launch_solve_int_batch(const BatchSolveArgs& b, hipStream_t s) {
-  hipLaunchKernelGGL(k_solve_int_batch, dim3(b.chan_off[b.n_arrays]), dim3(kSolveMainThreads), 0, s, b);
-  return hipGetLastError();
-}
-
 hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
   if (!solve_supported(a.Na, a.fmt, a.n_pix)) return hipErrorInvalidValue;
   if (solve_by_wave(a)) {
@@ -179,15 +143,7 @@ hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   if (a.n_pix > 1) return launch_solve_pixels(a, s);
-  if (solve_by_int(a)) {
-    const dim3 grid(a.F), blk(kSolveMainThreads);
-    const bool one = a.Na <= kSolveMainThreads;
-    if (a.fmt == kCI4 && one) hipLaunchKernelGGL((k_solve_int<kCI4, 1>), grid, blk, 0, s, a);
-    else if (a.fmt == kCI4) hipLaunchKernelGGL((k_solve_int<kCI4, 2>), grid, blk, 0, s, a);
-    else if (one) hipLaunchKernelGGL((k_solve_int<kCI8, 1>), grid, blk, 0, s, a);
-    else hipLaunchKernelGGL((k_solve_int<kCI8, 2>), grid, blk, 0, s, a);
-    return hipGetLastError();
-  }
+  if (solve_by_int(a)) return launch_solve_int(a, s);
   const int j = solve_main_j(a.Na);
   return j == 1 ? launch_solve_j<1>(a, s) : j == 2 ? launch_solve_j<2>(a, s) : launch_solve_j<4>(a, s);
 }

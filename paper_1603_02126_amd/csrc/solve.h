@@ -159,9 +159,12 @@ struct MainStageMax {
 // every antenna (zero when flagged) is written to a.u_hist, the values that
 // launch_hist_to_u would derive from the gain history, with coherent (sc1)
 // stores; once every wave's stores have completed, progress[f] = intervals
-// published, an agent-scope store the imaging workgroups poll.
+// published (n0 of them before this call, and with u_done the first one's u
+// too), an agent-scope store the imaging workgroups poll (none does where
+// progress is null).
 template <int J, int PS, int FMT, int T = kSolveMainThreads, bool PUBLISH = false>
-__device__ __forceinline__ void solve_channel_fmt(const SolveArgs& a, int f, uint8_t* smem, int* progress = nullptr) {
+__device__ __forceinline__ void solve_channel_fmt(const SolveArgs& a, int f, uint8_t* smem, int* progress = nullptr,
+                                                  int n0 = 0, bool u_done = false) {
   uint8_t (*chunk)[kSolveChunkBytes] = reinterpret_cast<uint8_t (*)[kSolveChunkBytes]>(smem);
   double2* P_l = reinterpret_cast<double2*>(smem + SolveSmem::P_OFF);
   double2* c_l = reinterpret_cast<double2*>(smem + SolveSmem::C_OFF);
@@ -233,7 +236,7 @@ __device__ __forceinline__ void solve_channel_fmt(const SolveArgs& a, int f, uin
           double2 c = zmul(A[j], make_double2(g[j].x * rr[j], -g[j].y * rr[j]));
           if (hold[j] & kHoldFlagged) c = make_double2(0.0, 0.0);
           c_l[an] = c;
-          if constexpr (PUBLISH) {
+          if (PUBLISH && !(u_done && n == 0)) {
             double2 u = zrecip(g[j]);
             if (hold[j] & kHoldFlagged) u = make_double2(0.0, 0.0);
             const float2 uf = make_float2(float(u.x), float(u.y));
@@ -249,8 +252,8 @@ __device__ __forceinline__ void solve_channel_fmt(const SolveArgs& a, int f, uin
     for (int j = 0; j < J; ++j) Kx[j] = Ky[j] = Q[j] = 0.0;
     __syncthreads();
     if constexpr (PUBLISH) {
-      if (tid == 0)
-        __hip_atomic_store((__attribute__((address_space(1))) int*)(progress + f), n + 1, __ATOMIC_RELAXED,
+      if (progress && tid == 0)
+        __hip_atomic_store((__attribute__((address_space(1))) int*)(progress + f), n0 + n + 1, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
     for (int r0 = 0; r0 < len; r0 += rpc) {

@@ -14,9 +14,17 @@
 //   correlation  rows = digits of P_re and P_im, contraction over 64 samples,
 //                columns = 16 bytes (two antennas in four lanes' columns).
 // The digit sums are exact in int32 and meet in FP64 at the end, so a sum is
-// rounded once (and its factors to 2^-62 of the largest) where an FP64 sum
-// rounds at every term.  What remains per interval is latency: five barriers,
-// the digits and the update.
+// rounded once where an FP64 sum rounds at every term.  Its factors are rounded
+// to 2^-61 of the largest of them, which keeps 53 bits of each while the c of
+// the antennas lie within 2^8 of each other (kDigitSpan).  They need not: an
+// antenna without a signal (K = Q = 0, g' = gamma g) has a c that grows by
+// 1 / gamma per interval, multiplies zeros only, and would take every digit from
+// the others' coefficients.  An interval whose c spread wider, and all after it,
+// go to the FP64 solve (solve_channel_fmt), which rounds each term by itself: 128
+// channels, 100 intervals of 100 samples, 256 antennas ci4, 439 us, with one
+// silent antenna 767 (in FP64 throughout 755).
+//   What remains per interval is latency: five barriers, the digits and the
+// update.
 // Largest error of P over the largest |P| against exact sums: 16 antennas 6.5e-17
 // (FP64 sums 1.5e-16), 256 6.6e-17 (3.3e-16), 900 8.6e-17 (4.6e-16).
 // 64 channels, 50 intervals, per interval, FP64 FMAs (four per sample in each
@@ -36,6 +44,8 @@ constexpr int kSolveIntMaxAnt = 1024;
 constexpr int64_t kSolveIntMinSamples = 20;   // of an interval
 constexpr int kSolveIntRows = 128;          // samples of a chunk at most
 constexpr int kRowBytes = 80;                // a block's row in the LDS: 64 bytes, padded
+constexpr int kDigitSpan = 8;                // exponents of the c of an interval
+constexpr uint32_t kWide = 0xffffffffu;      // in place of the largest |P| (abs_hi): the c spread wider
 constexpr int kDigitBlock = 16 * 16 + 16;   // bytes: 16 digit rows x 16 contraction entries, padded
 
 struct SolveIntSmem {
@@ -89,8 +99,10 @@ __device__ __forceinline__ double digit_sum(ivec4 d) {
   return fma(fma(fma(double(d[3]), 256.0, double(d[2])), 256.0, double(d[1])), 256.0, double(d[0]));
 }
 
+// Returns the number of intervals solved: n_int, or fewer where the next one's
+// c spread too wide (the gains are then those at its start; its u is written).
 template <int FMT, int J, bool PUBLISH>
-__device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uint8_t* smem, int* progress = nullptr) {
+__device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint8_t* smem, int* progress = nullptr) {
   static_assert(FMT == kCI4 || FMT == kCI8, "integer samples");
   using L = SolveIntSmem;
   constexpr int T = kSolveMainThreads, W = T / 64;
@@ -224,6 +236,7 @@ __device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uin
   // for every interval in the recurrence's way
   while (true) {
     const bool more = n + 1 < a.n_int, ends = i + 1 == (more ? full : last).nch;
+    uint32_t mp = 0u;                          // largest |P|, or kWide
     if (i == 0) {
     // c_a = A_a u_a / Na = A_a conj(g_a) r_a, u_a = 1 / g_a (zero for flagged antennas)
     double2 c[J];
@@ -258,10 +271,13 @@ __device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uin
     hc = max8(mx_c);
     const bool finite = hc < 0x7ff00000u;      // uniform
     const int sc = digit_scale(hc);
+    // a magnitude from 1 to `below` lies under the span
+    const uint32_t below = finite && int(hc >> 20) > kDigitSpan ? (((hc >> 20) - kDigitSpan) << 20) - 1u : 0u;
     static_for<0, J>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
       const int an = tid + T * j;
       if (an < Na) {
+        if (max(abs_hi(c[j].x), abs_hi(c[j].y)) - 1u < below) mp = kWide;
         const double x = finite ? c[j].x : 0.0, y = finite ? c[j].y : 0.0;
         const long long iy = fixed_point(y, sc);
         const unsigned long long dx = digits(fixed_point(x, sc)), dy = digits(iy), dn = digits(-iy);
@@ -284,7 +300,6 @@ __device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uin
     if (nr_next) request(t + nr, nr_next);
     {
       // taps of 16 samples per wave
-      uint32_t mp = 0u;
       for (int tile = wave; 16 * tile < nr; tile += W) {
         const int r = 16 * tile + m16;
         const uint8_t* bp = CH + r * kRowBytes + 16 * g16;
@@ -316,6 +331,7 @@ __device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uin
       if (lane == 63) mx_p[wave] = mp;
       __syncthreads();
       const uint32_t hp = max8(mx_p);
+      if (hp == kWide) break;                  // uniform
       const bool pfinite = hp < 0x7ff00000u;
       const int sp = digit_scale(hp);
       {
@@ -420,8 +436,8 @@ __device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uin
         gstore(a.g_hist + (int64_t(n + 1) * a.F + f) * Na + an, g[j]);
       }
     });
-    if (!more) break;
     ++n;
+    if (!more) break;
     }
     i = ends ? 0 : i + 1;
     t += nr;
@@ -439,12 +455,33 @@ __device__ __forceinline__ void solve_channel_int(const SolveArgs& a, int f, uin
     }
   });
   __syncthreads();
+  return n;
 }
 
-template <int J, bool PUBLISH>
-__device__ __forceinline__ void solve_channel_int_fmt(const SolveArgs& a, int f, uint8_t* smem, int* progress = nullptr) {
-  if (a.fmt == kCI4) solve_channel_int<kCI4, J, PUBLISH>(a, f, smem, progress);
-  else solve_channel_int<kCI8, J, PUBLISH>(a, f, smem, progress);
+// A copy of uniform arguments in scalar registers, for functions that are called.
+template <typename T>
+__device__ __forceinline__ T uniform_copy(const T& a) {
+  static_assert(sizeof(T) % 4 == 0, "word-wise copy");
+  T r;
+  uint32_t words[sizeof(T) / 4];
+  __builtin_memcpy(words, &a, sizeof(T));
+  static_for<0, int(sizeof(T) / 4)>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    words[i] = __builtin_amdgcn_readfirstlane(words[i]);
+  });
+  __builtin_memcpy(&r, words, sizeof(T));
+  return r;
+}
+
+// The arguments of the run from interval n on.
+__device__ __forceinline__ SolveArgs from_interval(SolveArgs a, int n) {
+  const int64_t t = int64_t(n) * a.t_cal, per = int64_t(a.F) * a.Na;
+  a.efield += t * per * (a.fmt == kCI4 ? 1 : a.fmt == kCI8 ? 2 : 8);
+  a.n_t -= t;
+  a.n_int -= n;
+  a.u_hist += n * per;
+  a.g_hist += n * per;
+  return a;
 }
 
 }  // namespace epic

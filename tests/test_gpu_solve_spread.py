@@ -1,0 +1,88 @@
+"""GPU: the calibration solve of integer samples where the antennas' tap
+coefficients c_a = A_a / (Na g_a) are of very different size, against the
+oracle's gain history: an antenna without a signal (its gain falls by gamma
+every interval while it multiplies zeros only), one that speaks up again after
+many such intervals, and start gains spread over many orders of magnitude; as
+launches of its own and inside the fused run (two arrays: always one launch)."""
+import numpy as np
+import pytest
+
+from paper_1603_02126_amd import synth
+
+from ._helpers import GAIN_RTOL, IMAGE_RTOL, gain_err, image_err, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(wl, packed, dev, overlap):
+    """The array twice in one plan (overlap: solve and imaging in one launch)."""
+    import torch
+    from paper_1603_02126_amd import lib
+    n_int = -(-wl.n_samples // wl.t_cal)
+    with lib.Plan([wl.array] * 2) as plan:
+        for i in range(2):
+            plan.set_model(i, wl.model_lmS, wl.cal_lm, wl.gamma, wl.t_cal)
+        plan.set_option(lib.OPT_OVERLAP, overlap)
+        e = torch.from_numpy(np.ascontiguousarray(packed)).to(dev)
+        gs = [torch.from_numpy(np.ascontiguousarray(wl.g0)).to(dev) for _ in range(2)]
+        imgs = [torch.zeros((wl.array.n_chan, wl.array.ny, wl.array.nx), dtype=torch.float32, device=dev) for _ in range(2)]
+        hs = [torch.zeros((n_int + 1, wl.array.n_chan, wl.array.n_ant), dtype=torch.complex128, device=dev) for _ in range(2)]
+        plan.run([e, e], wl.n_samples, gs, imgs, gain_hist=hs)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(hs[0].cpu().numpy(), hs[1].cpu().numpy())
+        return hs[0].cpu().numpy(), imgs[0].cpu().numpy()
+
+
+@pytest.mark.parametrize("overlap", [0, 1])
+@pytest.mark.parametrize("na,efmt,t_cal,n_int,gamma", [
+    (48, synth.FMT_CI8, 20, 100, 0.5), (48, synth.FMT_CI4, 20, 100, 0.1), (48, synth.FMT_CI8, 20, 100, 0.1),
+    (33, synth.FMT_CI4, 150, 70, 0.5),      # several chunks of samples per interval
+    (700, synth.FMT_CI8, 60, 30, 0.1),      # two antennas per thread, several chunks
+])
+def test_silent_antenna_leaves_the_others_alone(cuda, overlap, na, efmt, t_cal, n_int, gamma):
+    n = 32 if na <= 256 else 128
+    wl = synth.config_small(n=n, efmt=efmt, n_ant=na, n_chan=1 if na > 256 else 2, n_samples=n_int * t_cal, t_cal=t_cal,
+                            gamma=gamma)
+    packed = synth.make_efield(wl)
+    packed[:, :, na // 3] = 0
+    ref = oracle_run(wl, packed)
+    hist, img = _run(wl, packed, cuda, overlap)
+    assert gain_err(hist, ref["gains"]) <= GAIN_RTOL
+    if gamma ** n_int > 1e-35:              # the silent antenna's u is finite in FP32
+        assert image_err(img, ref["image"]).max() <= IMAGE_RTOL
+
+
+@pytest.mark.parametrize("overlap", [0, 1])
+@pytest.mark.parametrize("efmt", [synth.FMT_CI8, synth.FMT_CI4])
+def test_antenna_speaks_up_after_silence(cuda, overlap, efmt):
+    """One sample of an antenna silent for 60 intervals: its tap is 2^60 times
+    the others'.  Antennas that are zero at that sample keep their gains'
+    accuracy through the interval (their K does not see it)."""
+    t_cal, n_int, late = 20, 61, 60
+    wl = synth.config_small(efmt=efmt, n_chan=2, n_samples=n_int * t_cal, t_cal=t_cal)
+    packed = synth.make_efield(wl)
+    packed[:, :, 10] = 0
+    t1 = late * t_cal + 7
+    packed[t1, :, :24] = 0
+    packed[t1, :, 10] = 1
+    ref = oracle_run(wl, packed)
+    hist, _ = _run(wl, packed, cuda, overlap)
+    others = [a for a in range(24) if a != 10]
+    assert gain_err(hist[:late + 1], ref["gains"][:late + 1]) <= GAIN_RTOL
+    assert gain_err(hist[:, :, others], ref["gains"][:, :, others]) <= GAIN_RTOL
+
+
+@pytest.mark.parametrize("overlap", [0, 1])
+@pytest.mark.parametrize("efmt", [synth.FMT_CI8, synth.FMT_CI4])
+def test_start_gains_of_any_size(cuda, overlap, efmt):
+    """Start gains from 1e-6 to 1e6.  The antennas with the largest c are
+    silent in the first interval, so that its taps come from the others."""
+    wl = synth.config_small(efmt=efmt, n_chan=2, n_samples=40, t_cal=20)
+    na = wl.array.n_ant
+    size = 10.0 ** np.linspace(-6, 6, na)
+    wl = wl.replace(g0=wl.g_true * size[None, :])
+    packed = synth.make_efield(wl)
+    packed[:20, :, :na // 2] = 0
+    ref = oracle_run(wl, packed)
+    hist, _ = _run(wl, packed, cuda, overlap)
+    assert gain_err(hist, ref["gains"]) <= GAIN_RTOL
