@@ -17,6 +17,7 @@
 
 #include "../../include/epic.h"
 #include "epic_internal.h"
+#include "splits.h"
 
 using epic::ImageArgs;
 using zc = std::complex<double>;
@@ -732,25 +733,6 @@ int slots_for(const ArrayPlan& ap, SplitUse use) {
   return (use == SplitUse::fused ? epic::kSmallBodyWaves : epic::small_waves(N, epic::small_apl(N, ap.h.na))) * (64 / N);
 }
 
-// Time splits per channel for a target of `wg` workgroups, keeping >= 8 frames
-// per slot; at 64 x 64 (the two-waves-per-SIMD engines: eight waves) >= 16
-// frames per wave, which repays a workgroup's set-up and reduction (the
-// 1000-sample differentiable workload: 31 splits 1.20 ms, 8 splits 1.08 ms),
-// rounded up to whole rounds of workgroups over the CUs (one imaging
-// workgroup per CU).
-int64_t splits_for_target(epic_plan_t p, const ArrayPlan& ap, int64_t T, int64_t wg) {
-  const int N = ap.h.nx;
-  const int64_t units = int64_t(ap.h.F) * units_for(ap);
-  int64_t s = (wg + units - 1) / units;
-  const int64_t per_split = N == 64 ? 8 * 16 : N >= 128 ? 8 : 8 * 4 * (64 / N);
-  s = std::min<int64_t>(s, std::max<int64_t>(1, T / per_split));
-  if (units * s > p->n_cu) {
-    const int64_t rounds = (units * s + p->n_cu - 1) / p->n_cu;
-    s = std::min<int64_t>((rounds * p->n_cu + units - 1) / units, std::max<int64_t>(1, T));
-  }
-  return std::max<int64_t>(1, s);
-}
-
 // Microseconds of one channel's solve of T samples inside the fused run, from
 // the times of the solves by themselves (the several-pixel one runs there at
 // half its threads).
@@ -771,72 +753,17 @@ double fused_solve_us(const ArrayPlan& ap, int64_t T) {
   return n_int * (1.5 + double((len + rows - 1) / rows) * (1.2 + 0.17 * double(blocks)));
 }
 
-// Time splits per channel from what a workgroup does: steps of `slots` frames,
-// and a set-up and reduction worth one step more in a launch of its own, three
-// (1.5 up to 32 x 32) as an item of the fused run.
-//   A launch of its own takes its rounds of workgroups over the CUs times
-//   (steps + 1): 32 x 32, 48 channels x 700: 5 splits 53 us, 4 62, 8 63, 11
-//   (the former rule's) 68; 64 x 64, 64 channels x 1000: 4 splits 221 us, 7
-//   (former) 253; 256 x 256, 2048 antennas, 64 channels x 250, with its solve:
-//   2 splits 2.05 ms, 16 (former) 2.19.
-//   The fused run's workgroups pull items one after another, those that solve
-//   from `late` steps on (their channel's solve): LWA shape 22 splits 4.66 ms,
-//   24 (former) 4.72, 16 4.77; 32 x 32, 75 channels x 1501: 16 splits 264 us, 23
-//   (former) 370.
-int splits_by_steps(epic_plan_t p, const ArrayPlan& ap, int64_t T, SplitUse use) {
-  const bool fused = use == SplitUse::fused;
-  const int N = ap.h.nx;
-  const int64_t units = int64_t(ap.h.F) * units_for(ap), slots = slots_for(ap, use), most = (T + slots - 1) / slots;
-  const double setup = !fused ? 1.0 : N <= 32 ? 1.5 : 3.0;
-  // the solve of a channel in steps
-  const double step_us = N <= 32 ? 5.0 : N == 64 ? 6.8 : slots == 2 ? 9.0 : 14.0;
-  const double late = fused_solve_us(ap, T) / step_us;
-  const int64_t solvers = std::min<int64_t>(ap.h.F, p->n_cu - 1);
-  // at most 256 frames in one FP32 accumulator, as the former rules had on the
-  // largest shapes: rounding grows with them (HERA shape, 1000: 4.8e-7, 250: 1.4e-7)
-  const int64_t least = (most + 255) / 256;
-  int64_t best = least;
-  double cost = std::numeric_limits<double>::max();
-  auto consider = [&](int64_t s) {
-    s = std::max(least, std::min(s, most));
-    const double len = double(((T + s - 1) / s + slots - 1) / slots) + setup;
-    const int64_t items = units * s;
-    double c;
-    if (!fused) {
-      c = double((items + p->n_cu - 1) / p->n_cu) * len;
-    } else {
-      // the earliest end of an item by which all are done; the first items
-      // wait for the solves to get through their samples
-      const double first = late / double(s), end = double(items) * len;
-      auto done = [&](double t) {
-        return double(p->n_cu - solvers) * std::floor(std::max(0.0, t - first) / len) +
-               double(solvers) * std::floor(std::max(0.0, t - late) / len);
-      };
-      const double t0 = (end + double(solvers) * std::min(late, end) + double(p->n_cu - solvers) * std::min(first, end)) / p->n_cu;
-      c = std::numeric_limits<double>::max();
-      for (int k = 0; k < 3; ++k) {
-        const double e1 = first + len * (std::floor(std::max(0.0, t0 - first) / len) + k),
-                     e2 = late + len * (std::floor(std::max(0.0, t0 - late) / len) + k);
-        for (double e : {e1, e2})
-          if (done(e + 1e-6 * len) >= double(items)) c = std::min(c, e);
-      }
-      if (c > 1e300) c = t0 + 2 * len;
-      c = std::max(c, late + len);   // a channel's last item waits for its last interval
-    }
-    // the partial images' reduction: a launch whose threads read them one after
-    // another, eight at a time, at 5 TB/s at best
-    c += double(s) * (0.04 + double(ap.h.F) * N * N * 4.0 / 5e6) / step_us;
-    if (c < cost) {
-      cost = c;
-      best = s;
-    }
-  };
-  for (int64_t k = 1; k <= 24; ++k) {
-    consider(k);
-    consider(k * p->n_cu / units);                 // k rounds of workgroups
-    consider((T + k * slots - 1) / (k * slots));   // k steps each
-  }
-  return int(best);
+// What the rules of splits.h need of an array.
+epic::SplitShape split_shape(epic_plan_t p, const ArrayPlan& ap, int64_t T, SplitUse use) {
+  epic::SplitShape d{};
+  d.N = ap.h.nx;
+  d.F = ap.h.F;
+  d.n_cu = p->n_cu;
+  d.units = int64_t(ap.h.F) * units_for(ap);
+  d.slots = slots_for(ap, use);
+  d.fused = use == SplitUse::fused;
+  d.solve_us = d.fused ? fused_solve_us(ap, T) : 0.0;
+  return d;
 }
 
 // Snapshots: splits of a channel's windows, and whether the waves of a
@@ -883,11 +810,11 @@ int pick_splits(epic_plan_t p, const ArrayPlan& ap, int64_t T, int tuned = 0, Sp
   if (use == SplitUse::image || use == SplitUse::fused) {
     // decided once per run length (the plan's options and tables bump the generation)
     SplitMemo& m = ap.memo[use == SplitUse::fused];
-    if (m.T != T || m.generation != p->generation) m = SplitMemo{T, p->generation, splits_by_steps(p, ap, T, use)};
+    if (m.T != T || m.generation != p->generation) m = SplitMemo{T, p->generation, epic::splits_by_steps(split_shape(p, ap, T, use), T)};
     return m.splits;
   }
   // aim for >= 2048 workgroups (8 per CU on 256 CUs)
-  return int(splits_for_target(p, ap, T, 2048));
+  return int(epic::splits_for_target(split_shape(p, ap, T, use), T, 2048));
 }
 
 }  // namespace
