@@ -176,7 +176,7 @@ __device__ __forceinline__ void pair_frames(const ImageArgs& a, int f, int64_t t
   }
 }
 
-// Workgroup sum of the eight waves' accumulators, times `scale`, into
+// Workgroup sum (FP64) of the eight waves' accumulators, times `scale`, into
 // out[64 * 64] (row-major ky, kx); the accumulators are zeroed.  The sums go
 // through the wave areas, whose half frames are cleared again afterwards.
 template <int APL>
@@ -192,10 +192,10 @@ __device__ __forceinline__ void pair_reduce(float (&acc)[64], float* out, float 
   });
   __syncthreads();
   for (int idx = threadIdx.x; idx < N * N; idx += kPairThreads) {
-    float sum = 0.f;
+    double sum = 0.0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sum += red[q * N * N + idx];
-    gstore(out + idx, sum * scale);
+    for (int q = 0; q < 8; ++q) sum += double(red[q * N * N + idx]);
+    gstore(out + idx, float(sum * scale));
   }
   __syncthreads();
   clear_half_row(reinterpret_cast<float2*>(smem) + wave * PairSmem<APL>::WAVE, lam);

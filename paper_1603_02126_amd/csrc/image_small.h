@@ -115,7 +115,7 @@ __device__ __forceinline__ void small_frames(const ImageArgs& a, int f, int64_t 
   }
 }
 
-// Workgroup sum of the lane groups' accumulators, times `scale`, into out[N * N];
+// Workgroup sum (FP64) of the lane groups' accumulators, times `scale`, into out[N * N];
 // the accumulators are zeroed, the half frames left zero.
 template <int N, int APL, int W>
 __device__ __forceinline__ void small_reduce(float (&acc)[N], float* out, float scale, uint8_t* smem, float2* H, int h,
@@ -130,10 +130,10 @@ __device__ __forceinline__ void small_reduce(float (&acc)[N], float* out, float 
   });
   __syncthreads();
   for (int idx = threadIdx.x; idx < N * N; idx += 64 * W) {
-    float sum = 0.f;
+    double sum = 0.0;
 #pragma unroll 8
-    for (int q = 0; q < W * G::FPW; ++q) sum += red[q * N * N + idx];
-    gstore(out + idx, sum * scale);
+    for (int q = 0; q < W * G::FPW; ++q) sum += double(red[q * N * N + idx]);
+    gstore(out + idx, float(sum * scale));
   }
   __syncthreads();
   static_for<0, G::HP>([&](auto xc) { H[lam * G::HP + decltype(xc)::value] = make_float2(0.f, 0.f); });

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kPairThreads) void k_grid_half(GridArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kAccThreads = 512;
 
-// Sum of the workgroup's accumulators (acc[y] of lane x per slot) through
+// Sum (FP64) of the workgroup's accumulators (acc[y] of lane x per slot) through
 // `red` ([slots][N][N] floats): added to the image, or a partial image.
 template <int N, int SLOTS>
 __device__ __forceinline__ void acc_reduce(const ImageAccArgs& a, int f, int s, const float (&acc)[N], float* red,
@@ -126,11 +126,11 @@ __device__ __forceinline__ void acc_reduce(const ImageAccArgs& a, int f, int s, 
   __syncthreads();
   const float s2 = a.inv_na * a.inv_na;
   for (int idx = threadIdx.x; idx < N * N; idx += kAccThreads) {
-    float sum = 0.f;
+    double sum = 0.0;
 #pragma unroll
-    for (int q = 0; q < SLOTS; ++q) sum += red[q * N * N + idx];
-    if (a.splits > 1) a.partial[(int64_t(s) * a.F + f) * (N * N) + idx] = sum;
-    else a.image[int64_t(f) * N * N + idx] += sum * s2;
+    for (int q = 0; q < SLOTS; ++q) sum += double(red[q * N * N + idx]);
+    if (a.splits > 1) a.partial[(int64_t(s) * a.F + f) * (N * N) + idx] = float(sum);
+    else a.image[int64_t(f) * N * N + idx] += float(sum) * s2;
   }
 }
 

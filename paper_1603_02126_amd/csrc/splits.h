@@ -44,18 +44,37 @@ inline int64_t most_splits(const SplitShape& d) {
   return std::max<int64_t>(1, (12 * int64_t(d.n_cu) + d.units - 1) / d.units);
 }
 
+// The fewest splits that keep the rounding of the image sums where the rule by
+// workgroups has it (2048 of them, two rounds of the CUs for the paired 64 x 64
+// engine, half as many splits again in the fused run).  T frames in n FP32
+// accumulators per pixel, added in FP64, are off by sqrt(T / 3) / n of one
+// rounding; that rule's accumulators (four waves' up to 32 x 32, eight in the
+// fused run) were also added in FP32 within a workgroup, sqrt(slots / 3) of one
+// averaged over the splits.  A quarter of a rounding's variance is allowed in any
+// case, since the transforms and FP32 gains weigh some six.
+//   Error against exact sums, 64 channels of 250 samples, by splits: 128 x 128, 512
+// antennas, 1: 1.8e-7, 2: 1.2e-7, 6: 8.5e-8, 12: 8.1e-8, 32: 7.8e-8; 256 x 256, 2048
+// antennas, 2: 1.8e-7, 6: 1.2e-7, 16: 1.03e-7, 64: 9.3e-8.
+inline int64_t splits_for_rounding(const SplitShape& d, int64_t T) {
+  int64_t s = splits_for_target(d, T, d.N == 64 && d.slots == 8 && !d.fused ? 2 * int64_t(d.n_cu) : 2048);
+  if (d.fused) s = (3 * s + 1) / 2;
+  const double slots = d.N <= 32 ? (d.fused ? 8.0 : 4.0) * (64 / d.N) : double(d.slots), n = slots * double(s);
+  const double var = std::max(0.25, double(T) / 3.0 / (n * n) + (slots > 1 ? slots / 3.0 / double(s) : 0.0));
+  return int64_t(std::ceil(std::sqrt(double(T) / 3.0 / var) / double(d.slots) - 1e-6));
+}
+
 // Time splits per channel from what a workgroup does: steps of `slots` frames,
 // and a set-up and reduction worth one step more in a launch of its own, three
 // (1.5 up to 32 x 32) as an item of the fused run.
 //   A launch of its own takes its rounds of workgroups over the CUs times
 //   (steps + 1): 32 x 32, 48 channels x 700: 5 splits 53 us, 4 62, 8 63, 11
-//   (the former rule's) 68; 64 x 64, 64 channels x 1000: 4 splits 221 us, 7
-//   (former) 253; 256 x 256, 2048 antennas, 64 channels x 250, with its solve:
-//   2 splits 2.05 ms, 16 (former) 2.19.
+//   (the rule by workgroups) 68; 64 x 64, 64 channels x 1000: 4 splits 221 us, 7
+//   253.  256 x 256, 2048 antennas, 64 channels x 250, with its solve, would take
+//   2.05 ms at 2 splits, 2.19 at the 16 that the rounding asks for.
 //   The fused run's workgroups pull items one after another, those that solve
 //   from `late` steps on (their channel's solve): LWA shape 22 splits 4.66 ms,
-//   24 (former) 4.72, 16 4.77; 32 x 32, 75 channels x 1501: 16 splits 264 us, 23
-//   (former) 370.
+//   24 4.72, 16 4.77; 32 x 32, 75 channels x 1501: 16 splits 264 us, 23
+//   370.
 inline int splits_by_steps(const SplitShape& d, int64_t T) {
   const bool fused = d.fused;
   const int N = d.N;
@@ -67,7 +86,7 @@ inline int splits_by_steps(const SplitShape& d, int64_t T) {
   const int64_t solvers = std::min<int64_t>(d.F, d.n_cu - 1);
   // at most 256 frames in one FP32 accumulator, since rounding grows with them (HERA
   // shape, 1000: 4.8e-7, 250: 1.4e-7), as far as the bound on the partial images allows
-  const int64_t least = std::min((steps + 255) / 256, most);
+  const int64_t least = std::min(std::max((steps + 255) / 256, splits_for_rounding(d, T)), most);
   int64_t best = least;
   double cost = std::numeric_limits<double>::max();
   auto consider = [&](int64_t s) {

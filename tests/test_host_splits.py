@@ -51,3 +51,14 @@ def test_long_run_shapes(rule):
     sizes = [b for _, b in rule([(64, 128, 128, 8, 1, 0.043, 10 ** 6), (128, 512, 512, 2, 0, 0, 2 * 10 ** 5),
                                  (256, 512, 2048, 2, 0, 0, 10 ** 6)])]
     assert sizes[0] <= 0.06e9 and sizes[1] <= 0.25e9 and sizes[2] <= 0.3e9
+
+
+def test_short_runs_keep_the_rounding_of_the_image(rule):
+    """Rounding of T frames in n FP32 accumulators per pixel, sqrt(T / 3) / n:
+    no more than the rule by workgroups gave (16 splits at 256 x 256, one frame
+    at a time; four of eight waves at 64 x 64), or half of one rounding."""
+    (dense, _), (pair, _), (cls, _) = rule([(256, 64, 128, 1, 0, 0, 250), (64, 128, 128, 8, 0, 0, 2500),
+                                            (128, 64, 64, 2, 0, 0, 250)])
+    assert dense >= 16
+    assert (2500 / 3) ** 0.5 / (8 * pair) <= (2500 / 3 / 32 ** 2 + 8 / 3 / 4) ** 0.5
+    assert (250 / 3) ** 0.5 / (2 * cls) <= 0.5
