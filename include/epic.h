@@ -255,16 +255,14 @@ int epical_set_denominator(epic_plan_t plan, int32_t array, const double* D);
  *                        on a plan-owned stream (ordered after and before the
  *                        caller's stream by events) and replays it while the
  *                        buffers and n_samples stay the same.
- *   EPIC_OPT_OVERLAP     1 (default) = where every array of the plan allows it
+ *   EPIC_OPT_OVERLAP     1 = where every array of the plan allows it
  *                        (no band; one tapped pixel with more than 64 antennas
  *                        or intervals longer than 8 samples, or several tapped
  *                        pixels with at most 512 antennas; an imaging engine of
  *                        the persistent kernel, the FFT transform) and the
  *                        plan's channels number fewer than the GPU's CUs (the
  *                        solve, one workgroup per channel, leaves CUs idle),
- *                        unless one array's solve is too short against its
- *                        imaging to be worth it (one tapped pixel, up to 64 x
- *                        64), epic_run makes one launch for the calibration solve
+ *                        epic_run makes one launch for the calibration solve
  *                        and the imaging: the solve of each channel publishes
  *                        each interval's calibration as soon as it is known and
  *                        the imaging of a time split starts once its intervals
@@ -273,7 +271,11 @@ int epical_set_denominator(epic_plan_t plan, int32_t array, const double* D);
  *                        (with one pixel gains bit for bit, with several the
  *                        same sums in another order; images within rounding).
  *                        Timing then counts the one launch as imaging.
- *                        0 = separate launches.  epic_run_noalloc never fuses. */
+ *                        0 = separate launches.  Left unset: as 1, except for a
+ *                        plan of one array (one tapped pixel, up to 64 x 64,
+ *                        no graph) whose solve is too short against its imaging
+ *                        for one launch to be worth it.  epic_run_noalloc never
+ *                        fuses. */
 #define EPIC_OPT_SPLITS 1
 #define EPIC_OPT_TRANSFORM 2
 #define EPIC_OPT_TIMING 3

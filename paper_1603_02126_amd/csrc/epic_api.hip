@@ -514,6 +514,8 @@ struct StageWorkspace {
 };
 constexpr int kStageStreams = 4;
 
+enum { kOverlapOff = 0, kOverlapOn = 1, kOverlapAuto = 2 };
+
 struct epic_plan_s {
   int device = 0;
   int n_cu = 256;
@@ -528,7 +530,8 @@ struct epic_plan_s {
   int transform = 0;
   int batch = 0;             // 0 auto (batched when >1 array), 1 on, 2 off
   bool graph = false;
-  bool overlap = true;       // the fused solve + imaging launch where every array allows it
+  int overlap = kOverlapAuto;   // the fused solve + imaging launch: never, where every array allows it, or
+                                // where it pays as well
   int fused_polls = epic::kFusedWaitPolls;   // bound of one wait of the fused run
   bool timing = false;
   std::vector<TimerRec> timers;
@@ -1211,8 +1214,8 @@ int epic_plan_set_option(epic_plan_t plan, int32_t key, int64_t value) {
       return EPIC_OK;
     case EPIC_OPT_OVERLAP:
       if (value != 0 && value != 1) return fail(EPIC_ERR_ARG, "EPIC_OPT_OVERLAP is 0 or 1");
-      if (plan->overlap != (value != 0)) plan->generation++;
-      plan->overlap = value != 0;
+      if (plan->overlap != int(value)) plan->generation++;
+      plan->overlap = int(value);
       return EPIC_OK;
     case EPIC_OPT_WAIT_POLLS:
       if (value < 0 || value > epic::kFusedWaitPolls)
@@ -1398,7 +1401,7 @@ static bool own_launch(epic_plan_t plan, const ArrayPlan& ap) { return body_of(p
 // the cost of finer imaging items (HERA shape, 512 channels: 23.0 against
 // 22.8 ms; eight uneven arrays of 256 channels: 61.3 against 61.1 ms).
 static bool fused_eligible(epic_plan_t plan) {
-  if (!plan->overlap || plan->arrays.size() > size_t(epic::kMaxBatch)) return false;
+  if (plan->overlap == kOverlapOff || plan->arrays.size() > size_t(epic::kMaxBatch)) return false;
   int n_chan = 0;
   for (const ArrayPlan& ap : plan->arrays) n_chan += ap.h.F;
   if (n_chan >= plan->n_cu) return false;
@@ -1763,7 +1766,7 @@ int epic_run(epic_plan_t plan, const void* const* efield, int64_t n_samples, dou
   bool all_batchable = false, any_band = false;
   const bool eligible = plan && plan->arrays.size() <= size_t(epic::kMaxBatch) && fused_eligible(plan);
   // (a captured run of one array is the one launch wherever that is possible)
-  const bool fused_plan = eligible && (plan->graph || plan->arrays.size() > 1 || plan->arrays[0].n_pix > 1 ||
+  const bool fused_plan = eligible && (plan->overlap == kOverlapOn || plan->graph || plan->arrays.size() > 1 || plan->arrays[0].n_pix > 1 ||
                                        fused_pays(plan->arrays[0], std::max<int64_t>(n_samples, 1)));
   int rc = prepare_run(plan, efield, n_samples, gains, image, gain_hist, ant_status, lay, need, all_batchable,
                        any_band, nullptr, fused_plan);
