@@ -372,7 +372,13 @@ int epic_grid(epic_plan_t plan, int32_t array, const void* efield, int64_t t0, i
  *   image[f][ky][kx] += sum_t |X_t(k)|^2     (not divided by nt)
  *   tap[t][f] = X_t(k0_f)                    (if tap != NULL; needs a model)
  * grid: device [nt][F][ny][nx] complex64; image: device [F][ny][nx] float32,
- * accumulated; tap: device [nt][F] complex64 or NULL.  Na = unflagged count. */
+ * accumulated; tap: device [nt][F] complex64 or NULL.  Na = unflagged count.
+ * Calls that divide a channel's samples over several workgroups keep partial
+ * images in workspaces of the plan: up to four, 1024 images of the plan's largest
+ * grid each (16 MiB at 64 x 64), allocated by the first calls that need them
+ * and freed with the plan.  A call on a fifth stream waits on the device for the
+ * workspace used longest ago.  A captured call uses none: one workgroup per
+ * channel. */
 int epic_image_accumulate(epic_plan_t plan, int32_t array, const float* grid, int32_t nt,
                           float* image, float* tap, epic_stream_t stream);
 

@@ -506,13 +506,14 @@ struct GraphKey {
   }
 };
 
-// Partial images of the stage-wise accumulate call, one per stream.
+// Partial images of a stage-wise accumulate call in flight.
 struct StageWorkspace {
-  hipStream_t stream = nullptr;
   void* mem = nullptr;
-  size_t bytes = 0;
+  hipEvent_t done = nullptr;   // recorded after the last call that used it
+  hipStream_t stream = nullptr;
+  uint64_t used = 0;           // number of that call
 };
-constexpr int kStageStreams = 4;
+constexpr int kStageWorkspaces = 4;
 
 enum { kOverlapOff = 0, kOverlapOn = 1, kOverlapAuto = 2 };
 
@@ -523,7 +524,8 @@ struct epic_plan_s {
   // scratch
   void* d_scratch = nullptr;
   size_t scratch_bytes = 0;
-  StageWorkspace stage_ws[kStageStreams];
+  StageWorkspace stage_ws[kStageWorkspaces];
+  uint64_t stage_calls = 0;
   uint64_t generation = 1;   // bumped whenever device tables or scratch move
   // options
   int splits = 0;
@@ -602,36 +604,59 @@ int plan_scratch(epic_plan_t p, size_t bytes, void** out) {
   return EPIC_OK;
 }
 
-// Workspace of the stage-wise accumulate call on stream `s` (its partial
-// images), or null: the call then runs without one, one workgroup per
-// channel.  Each stream has its own, so calls on several streams stay
-// independent: the first kStageStreams streams of a plan, kept until the plan
-// goes.  A captured call gets none, since its replays may run on any stream.
-float* stage_workspace(epic_plan_t p, hipStream_t s, size_t bytes) {
+// A workspace for a stage-wise accumulate call on stream `s`, or null: the call
+// then runs without one, one workgroup per channel.  Streams keep to one each
+// while there are enough, so that their calls run side by side; beyond that the
+// one used longest ago passes on.  The call waits on the device for the event after
+// the workspace's last use, also where that was on a stream of the same handle: it
+// may be a new one, the old destroyed with work still to do.  Only the null stream
+// is always the same; its event is recorded when another stream takes over (with
+// an event per call the stage-wise loop of 64 channels x 100 at 64 x 64 took 143.5
+// us, so 140.0).
+// Every workspace has the size of the plan's largest call (16 MiB at 64 x 64), is
+// allocated at its first use and kept until the plan goes.  A captured call gets
+// none, since its replays may run on any stream.
+StageWorkspace* stage_workspace(epic_plan_t p, hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
     return nullptr;
   }
-  for (StageWorkspace& w : p->stage_ws) {
-    if (w.mem && w.stream != s) continue;
-    if (bytes > w.bytes) {
-      if (w.mem) {
-        if (hipStreamSynchronize(s) != hipSuccess) return nullptr;   // an earlier call may still use it
-        hipFree(w.mem);
-        w = StageWorkspace{};
-      }
-      if (hipMalloc(&w.mem, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        w = StageWorkspace{};
-        return nullptr;
-      }
-      w.stream = s;
-      w.bytes = bytes;
+  StageWorkspace* w = &p->stage_ws[0];
+  for (StageWorkspace& c : p->stage_ws) {
+    if (c.mem && c.stream == s) {
+      w = &c;
+      break;
     }
-    return static_cast<float*>(w.mem);
+    if (c.used < w->used) w = &c;   // (not allocated: 0)
   }
-  return nullptr;
+  if (!w->mem) {
+    size_t cells = 0;
+    for (const ArrayPlan& ap : p->arrays)
+      if (ap.h.nx <= 64) cells = std::max(cells, size_t(ap.h.nx) * ap.h.ny);
+    // (allowed while another stream of the thread is captured)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipError_t e = hipEventCreateWithFlags(&w->done, hipEventDisableTiming | hipEventDisableSystemFence);
+    if (e == hipSuccess) e = hipMalloc(&w->mem, cells * epic::kAccMaxPartials * sizeof(float));
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      if (w->done) hipEventDestroy(w->done);
+      *w = StageWorkspace{};
+      return nullptr;
+    }
+  } else if (s || w->stream) {
+    hipError_t e = w->stream ? hipSuccess : hipEventRecord(w->done, nullptr);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s, w->done, 0);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+  }
+  w->stream = s;
+  w->used = ++p->stage_calls;
+  return w;
 }
 
 int check_plan(epic_plan_t p, int array) {
@@ -1021,7 +1046,10 @@ int epic_plan_destroy(epic_plan_t plan) {
   hipDeviceSynchronize();
   for (auto& ap : plan->arrays) free_array(ap);
   hipFree(plan->d_scratch);
-  for (auto& w : plan->stage_ws) hipFree(w.mem);
+  for (auto& w : plan->stage_ws) {
+    hipFree(w.mem);
+    if (w.done) hipEventDestroy(w.done);
+  }
   for (auto& t : plan->timers) {
     hipEventDestroy(t.a);
     hipEventDestroy(t.b);
@@ -1282,12 +1310,16 @@ int epic_image_accumulate(epic_plan_t plan, int32_t array, const float* grid, in
   if (ap.h.na_eff < 1) return fail(EPIC_ERR_ARG, "all antennas are flagged");
   hipStream_t s = static_cast<hipStream_t>(stream);
   int splits = epic::image_acc_splits(ap.h.nx, ap.h.F, nt, plan->n_cu);
-  const size_t need = size_t(splits) * ap.h.F * ap.h.nx * ap.h.ny * sizeof(float);
-  float* partial = splits > 1 ? stage_workspace(plan, s, need) : nullptr;
-  if (!partial) splits = 1;
+  StageWorkspace* ws = splits > 1 ? stage_workspace(plan, s) : nullptr;
+  if (!ws) splits = 1;
   epic::ImageAccArgs a{reinterpret_cast<const float2*>(grid), nt, ap.h.F, float(1.0 / ap.h.na_eff), image,
-                       reinterpret_cast<float2*>(tap), tap ? ap.d_k0 : nullptr, splits, partial};
+                       reinterpret_cast<float2*>(tap), tap ? ap.d_k0 : nullptr, splits,
+                       ws ? static_cast<float*>(ws->mem) : nullptr};
   hipError_t e = epic::launch_image_acc(ap.h.nx, a, s);
+  if (ws && s) {
+    const hipError_t r = hipEventRecord(ws->done, s);
+    if (e == hipSuccess) e = r;
+  }
   return e == hipSuccess ? EPIC_OK : hip_fail(e, "epic_image_accumulate launch");
 }
 

@@ -91,3 +91,27 @@ def test_epical_update_sample_split(cuda, na, nt, efmt):
         K, Q = O.correlate(E[:, f], tap[:, f].astype(np.complex128))
         want, _ = O.gain_update(K / nt, Q / nt, s["A"], s["D"], g0[f], s["na"], wl.gamma)
         assert np.abs(got[f] - want).max() <= 1e-9 * np.abs(want).max()
+
+
+def test_accumulate_on_more_streams_than_workspaces(cuda):
+    """Seven streams in turn, the null stream among them: the same image bits on
+    each, whether a stream has a workspace of its own or takes another's over."""
+    import torch
+    n, n_chan = 64, 5
+    wl = synth.config_small(n=n, n_chan=n_chan, n_ant=40)
+    gen = torch.Generator(device=cuda).manual_seed(5)
+    grid = torch.randn(200, n_chan, n, n, dtype=torch.complex64, device=cuda, generator=gen)
+    img = torch.zeros(16, n_chan, n, n, device=cuda)
+    streams = [torch.cuda.Stream() for _ in range(6)] + [torch.cuda.default_stream()]
+    torch.cuda.synchronize()
+    with _lib().Plan([wl.array]) as plan:
+        for k in range(14):
+            with torch.cuda.stream(streams[(3 * k) % 7 if k < 7 else k % 7]):
+                plan.image_accumulate(0, grid[:100], img[k])
+        with torch.cuda.stream(streams[2]):
+            plan.image_accumulate(0, grid, img[14])       # more samples than the calls before
+        plan.image_accumulate(0, grid, img[15])
+        torch.cuda.synchronize()
+    for k in range(1, 14):
+        assert torch.equal(img[k], img[0]), k
+    assert torch.equal(img[14], img[15])
