@@ -450,16 +450,9 @@ void* static_scratch_ptr(int dev, hipError_t* err) {
 // ---------------------------------------------------------------------------
 // plan
 // ---------------------------------------------------------------------------
-// The time splits last worked out for an array (pick_splits).
-struct SplitMemo {
-  int64_t T = -1;
-  uint64_t generation = 0;
-  int splits = 1;
-};
-
 struct ArrayPlan {
   HostArray h;
-  mutable SplitMemo memo[2];
+  mutable epic::SplitMemo memo;
   uint32_t* d_cell_ixy = nullptr;
   float* d_cell_w = nullptr;
   uint2* d_slots = nullptr;   // gridding schedule of the imaging engine
@@ -835,12 +828,7 @@ SnapPlan snap_plan(epic_plan_t p, const ArrayPlan& ap, int64_t T, int64_t t_acc)
 int pick_splits(epic_plan_t p, const ArrayPlan& ap, int64_t T, int tuned = 0, SplitUse use = SplitUse::other) {
   if (tuned > 0) return int(std::max<int64_t>(1, std::min<int64_t>(tuned, std::max<int64_t>(1, T))));
   if (p->splits > 0) return int(std::max<int64_t>(1, std::min<int64_t>(p->splits, std::max<int64_t>(1, T))));
-  if (use == SplitUse::image || use == SplitUse::fused) {
-    // decided once per run length (the plan's options and tables bump the generation)
-    SplitMemo& m = ap.memo[use == SplitUse::fused];
-    if (m.T != T || m.generation != p->generation) m = SplitMemo{T, p->generation, epic::splits_by_steps(split_shape(p, ap, T, use), T)};
-    return m.splits;
-  }
+  if (use == SplitUse::image || use == SplitUse::fused) return ap.memo.get(split_shape(p, ap, T, use), T);
   // aim for >= 2048 workgroups (8 per CU on 256 CUs)
   return int(epic::splits_for_target(split_shape(p, ap, T, use), T, 2048));
 }

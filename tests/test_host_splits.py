@@ -26,6 +26,7 @@ def rule(tmp_path_factory):
         out = [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
         assert len(out) == len(cases)
         return out
+    run.exe = exe
     return run
 
 
@@ -62,3 +63,9 @@ def test_short_runs_keep_the_rounding_of_the_image(rule):
     assert dense >= 16
     assert (2500 / 3) ** 0.5 / (8 * pair) <= (2500 / 3 / 32 ** 2 + 8 / 3 / 4) ** 0.5
     assert (250 / 3) ** 0.5 / (2 * cls) <= 0.5
+
+
+@pytest.mark.parametrize("lengths,worked", [(1, 1), (2, 2), (8, 8), (9, 1000)])
+def test_alternating_run_lengths_are_worked_out_once(rule, lengths, worked):
+    r = subprocess.run([rule.exe, str(lengths)], capture_output=True, text=True, check=True, timeout=60)
+    assert int(r.stdout) == worked
