@@ -40,6 +40,11 @@ __device__ __forceinline__ ImageArgs uniform_args(const ImageArgs& a, int4& w) {
   return r;
 }
 
+template <int N, int APL>
+__device__ __noinline__ void fft8_call(const ImageArgs& a, int4 w, uint8_t* smem) {
+  const ImageArgs la = uniform_args(a, w);
+  image_item<N, APL, kSmallBodyWaves>(la, w.y, w.w, smem);
+}
 template <int N, int APL, int FMT>
 __device__ __noinline__ void small_call(const ImageArgs& a, int4 w, uint8_t* smem) {
   const ImageArgs la = uniform_args(a, w);
@@ -62,18 +67,20 @@ __device__ __noinline__ void dense_call(const ImageArgs& a, int4 w, uint8_t* sme
 }
 
 // Body codes: 1000 kind + parameters (0: no body, the array has its own launch).
+constexpr int fft8_code(int N, int apl) { return 1000 + 10 * N + apl; }
 constexpr int small_code(int N, int apl, int fmt) { return 10000 + 100 * N + 10 * apl + fmt; }
 constexpr int pair_code(int apl, int fmt) { return 2000 + 10 * apl + fmt; }
 constexpr int cls_pair_code(int R, int fmt, bool db) { return 3000 + 100 * R + 10 * fmt + (db ? 1 : 0); }
 constexpr int dense_code(int R, int fmt, int gb) { return 4000 + 100 * R + 10 * fmt + gb; }
 
 static_assert(kBatchThreads == 64 * kSmallBodyWaves, "the small-grid body's waves");
-static_assert(SmallSmem<32, 8, 8>::BYTES <= kLdsBytes && SmallSmem<16, 8, 8>::BYTES <= kLdsBytes && PairSmem<4>::BYTES <= kLdsBytes && ClsPairSmem<4>::BYTES <= kLdsBytes &&
+static_assert(FftSmem<32, 2, 8>::BYTES <= kLdsBytes && SmallSmem<32, 8, 8>::BYTES <= kLdsBytes && SmallSmem<16, 8, 8>::BYTES <= kLdsBytes && PairSmem<4>::BYTES <= kLdsBytes && ClsPairSmem<4>::BYTES <= kLdsBytes &&
                   ClsPairSmem<4, true>::BYTES <= kLdsBytes && ClsDenseSmem<4>::BYTES <= kLdsBytes,
               "every body fits the shared LDS arena");
 
 __device__ __forceinline__ void run_item(const ImageArgs& a, int code, int4 w, uint8_t* smem) {
   switch (code) {
+    case fft8_code(32, 2): fft8_call<32, 2>(a, w, smem); break;
     case small_code(16, 2, kCI8): small_call<16, 2, kCI8>(a, w, smem); break;
     case small_code(16, 2, kCI4): small_call<16, 2, kCI4>(a, w, smem); break;
     case small_code(16, 2, kCF32): small_call<16, 2, kCF32>(a, w, smem); break;

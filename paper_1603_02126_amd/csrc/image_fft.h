@@ -15,8 +15,8 @@ struct FftSmem {
 };
 
 // One work item of the N <= 64 FFT engine: channel f, time split s; W waves
-// (4 in its own kernel; 8, two per SIMD, in the persistent batched kernel,
-// for N <= 32 where eight waves' frame buffers fit).
+// (4 in its own kernel; 8, two per SIMD, in the persistent kernels at 32 x 32
+// with up to 64 antennas, where eight waves' frame buffers fit).
 template <int N, int APL, int W = 4>
 __device__ __forceinline__ void image_item(const ImageArgs& a, int f, int s, uint8_t* smem) {
   using G = Geo<N, W>;
@@ -59,7 +59,7 @@ __device__ __forceinline__ void image_item(const ImageArgs& a, int f, int s, uin
     add_norms<N>(acc, v);
   }
 
-  // workgroup reduction of the SLOTS accumulators
+  // workgroup sum (FP64) of the SLOTS accumulators
   __syncthreads();
   float* red = reinterpret_cast<float*>(lds);
   static_for<0, N>([&](auto yc) {
@@ -69,10 +69,10 @@ __device__ __forceinline__ void image_item(const ImageArgs& a, int f, int s, uin
   __syncthreads();
   float* out = a.partial + (int64_t(s) * a.F + f) * (N * N);
   for (int idx = threadIdx.x; idx < N * N; idx += 64 * W) {
-    float sum = 0.f;
+    double sum = 0.0;
 #pragma unroll
-    for (int q = 0; q < G::SLOTS; ++q) sum += red[q * N * N + idx];
-    gstore(out + idx, sum);
+    for (int q = 0; q < G::SLOTS; ++q) sum += double(red[q * N * N + idx]);
+    gstore(out + idx, float(sum));
   }
   __syncthreads();
 }

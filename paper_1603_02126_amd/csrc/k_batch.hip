@@ -7,13 +7,14 @@
 //                   group, time split} from an atomic counter (items sorted
 //                   by cost, largest first) and runs the body chosen for that
 //                   array in one LDS arena:
-//                     N <= 32     the FFT engine with eight waves
-//                     N = 64      the paired engine (integer E-fields, <= 256 antennas)
+//                     N <= 32     the half-frame engine with eight waves, or (32 x 32,
+//                                 <= 64 antennas) the whole-frame FFT engine
+//                     N = 64      the paired engine (<= 256 antennas)
 //                     N = 128/256 the class-pair engine (<= 512 antennas) or the
 //                                 dense class engine (<= 2048 / 1024)
 //   k_reduce_batch  FP64 reduction of every array's partial images
-// Arrays no body covers (complex float E-fields at 64 x 64 and above, the
-// DFT-GEMM form) are imaged by their own launches in the same sequence.
+// Arrays no body covers (64 x 64 with more than 256 antennas, 128 x 128 with more
+// than 1024, the DFT-GEMM form) are imaged by their own launches in the same sequence.
 // Per-array arguments travel in the kernel argument block; the item list is
 // plan-owned device memory.  The whole sequence (plus the counter reset) is
 // what the library captures in a hipGraph.  The bodies (batch_bodies.h) are
@@ -53,8 +54,15 @@ __global__ __launch_bounds__(kBatchThreads) void k_image_batch(BatchImageArgs b)
   }
 }
 
+// Up to 64 antennas at 32 x 32 the whole-frame engine is the faster of the two
+// with eight waves: one LDS pass over the frame instead of two halves, and with
+// few antennas its frames and staging still fit.  One split of 200 channels x 300
+// in the fused run, 40 antennas ci8 115 us with half frames, 104 with whole ones,
+// 64 antennas cf32 124 and 110; with 100 antennas 124 against 141, and at 16 x 16
+// with 32 antennas 64 against 66 (three splits).
 int batch_body(const ImageArgs& a, int N, bool dft) {
   if (dft) return 0;
+  if (N == 32 && apl_for(N, a.Na) == 2 && a.n_slots <= Budget<32, 2, kSmallBodyWaves>::TAB_SLOTS) return fft8_code(32, 2);
   if (small_engine(a, N, kSmallBodyWaves)) return small_code(N, apl_for(N, a.Na), a.fmt);
   if (N == 64) return pair_engine(a, N) ? pair_code(apl_for(N, a.Na), a.fmt) : 0;
   if (N == 128 || N == 256) {

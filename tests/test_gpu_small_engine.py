@@ -80,3 +80,30 @@ def test_small_adjoint_matches_oracle(cuda, n, na, efmt, kernel, n_samples):
     ref = _oracle_grad(wl, packed, g.astype(np.complex64).astype(np.complex128), M, [0, 1])
     assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
     plan.close()
+
+
+@pytest.mark.parametrize("na,efmt", [(7, CF32), (32, CI4), (64, CI8), (65, CI8)])
+def test_persistent_kernels_at_32(cuda, na, efmt):
+    """The persistent kernels' bodies at 32 x 32 around 64 antennas (whole frames
+    up to there, half frames beyond), fused and batched, with one sample past a
+    step of 16 frames and several splits."""
+    import torch
+    from paper_1603_02126_amd import lib
+    wl = synth.config_small(n=32, efmt=efmt, n_ant=na, n_chan=2, n_samples=49, t_cal=10)
+    packed = synth.make_efield(wl)
+    ref = oracle_run(wl, packed)
+    e = torch.from_numpy(np.ascontiguousarray(packed)).to(cuda)
+    for overlap in (1, 0):
+        for splits in (0, 3):
+            with lib.Plan([wl.array] * 2) as plan:
+                plan.set_option(lib.OPT_OVERLAP, overlap)
+                plan.set_option(lib.OPT_SPLITS, splits)
+                for i in range(2):
+                    plan.set_model(i, wl.model_lmS, wl.cal_lm, wl.gamma, wl.t_cal)
+                gs = [torch.from_numpy(np.ascontiguousarray(wl.g0)).to(cuda) for _ in range(2)]
+                imgs = [torch.zeros((2, 32, 32), dtype=torch.float32, device=cuda) for _ in range(2)]
+                plan.run([e, e], wl.n_samples, gs, imgs)
+                torch.cuda.synchronize()
+            for i in range(2):
+                assert gain_err(gs[i].cpu().numpy(), ref["gains"][-1]) <= GAIN_RTOL
+                assert image_err(imgs[i].cpu().numpy(), ref["image"]).max() <= IMAGE_RTOL
