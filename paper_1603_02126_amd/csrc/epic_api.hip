@@ -1944,6 +1944,9 @@ int epic_run_snapshots(epic_plan_t plan, int32_t array, const void* efield, int6
     return fail(EPIC_ERR_UNSUPPORTED, "calibration solve supports Na <= 2048 and Na * bytes per sample <= 16 KiB");
   if (n_samples < 1) return fail(EPIC_ERR_ARG, "n_samples must be >= 1");
   if (t_acc < 1) return fail(EPIC_ERR_ARG, "t_acc must be >= 1");
+  // one window either way; the engines that keep their lanes in step walk t_acc
+  // samples per window, present or not
+  t_acc = std::min(t_acc, n_samples);
   if (!efield || !gains || !images) return fail(EPIC_ERR_ARG, "efield, gains and images must not be NULL");
   if ((rc = check_aligned({{efield, "efield"}, {gains, "gains"}, {images, "images"}, {gain_hist, "gain_hist"},
                            {ant_status, "ant_status"}})))

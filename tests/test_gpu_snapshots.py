@@ -137,3 +137,15 @@ def test_snapshots_follow_band_and_pixel_calibration(cuda, mode):
     np.testing.assert_array_equal(gh, run["hist"])
     mean = snaps.astype(np.float64).mean(axis=0)
     assert image_err(mean, run["image"]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("n,na,n_samples", [(16, 20, 1), (32, 100, 30), (64, 100, 30), (64, 300, 9)])
+def test_window_far_longer_than_the_run(cuda, n, na, n_samples):
+    """One window, in time set by the samples there are."""
+    wl = synth.config_small(n=n, efmt=synth.FMT_CI8, n_ant=na, n_chan=2, n_samples=n_samples, t_cal=10)
+    packed = synth.make_efield(wl)
+    got, gh = _gpu_snap(wl, packed, 1 << 62, cuda)
+    ref, rg = _oracle_snap(wl, packed, n_samples)
+    assert got.shape == ref.shape == (1, 2, n, n)
+    assert gain_err(gh, rg) <= GAIN_RTOL
+    assert _window_err(got, ref) <= IMAGE_RTOL
