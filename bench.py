@@ -48,10 +48,10 @@ PEAK_HBM_GBS = 8000.0
 # per dispatch), each scaled by what the same counter reads for a plain 256 MiB
 # device copy (FETCH x2.000, WRITE x1.000).  Valid only for the sources that
 # determine the imaging kernels' code and their launch configuration (the time
-# splits, chosen in epic_api.hip), as they were when the counters were taken:
+# splits, chosen in epic_api.hip by the rules of splits.h), as they were when the counters were taken:
 # any change to one of them makes the figure stale and it is reported as null.
 TRAFFIC_SOURCES = ("k_image.hip", "image_fft.h", "image_cls.h", "engine.h", "fft_reg.h", "xpose.h", "epic_internal.h",
-                   "epic_api.hip")
+                   "epic_api.hip", "splits.h")
 TRAFFIC_MEASURED = {
     "lwa": {"sources_sha256": "2eed0b3419fffb730fe00e12a0d64eaa126ae41e15e5f36ddfc296204d9416e4",
             "fetch_kib": 173354.0, "fetch_scale": 2.000, "write_kib": 12288.0, "write_scale": 1.000},

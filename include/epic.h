@@ -254,7 +254,11 @@ int epical_set_denominator(epic_plan_t plan, int32_t array, const double* D);
  *   EPIC_OPT_GRAPH       1 = epic_run captures its batched launches in a hipGraph
  *                        on a plan-owned stream (ordered after and before the
  *                        caller's stream by events) and replays it while the
- *                        buffers and n_samples stay the same.
+ *                        buffers and n_samples stay the same.  Taken: plans in
+ *                        the batched form, and one array whose run is one launch
+ *                        (EPIC_OPT_OVERLAP), of cf32 samples at 64 x 64 and above
+ *                        only with EPIC_OPT_BATCH = 1; others give
+ *                        EPIC_ERR_UNSUPPORTED from epic_run.
  *   EPIC_OPT_OVERLAP     1 = where every array of the plan allows it
  *                        (no band; one tapped pixel with more than 64 antennas
  *                        or intervals longer than 8 samples, or several tapped

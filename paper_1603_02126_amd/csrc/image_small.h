@@ -11,9 +11,11 @@
 //
 // What bounds it: vector issue and LDS traffic, half and half, once enough
 // waves overlap their LDS phases with each other's FFTs.  Half frames let a
-// workgroup hold kSmallWaves waves, three or four per SIMD, where whole frames
-// (image_fft.h image_item, kept for schedules whose table does not fit here)
-// left room for one or two.
+// workgroup hold small_waves() waves, three or four per SIMD, where whole frames
+// (image_fft.h image_item) leave room for one or two.  Those are kept for
+// schedules whose table does not fit here, and in the persistent kernels, whose
+// eight waves are two per SIMD either way, for up to 64 antennas at 32 x 32
+// (batch_body).
 #pragma once
 #include "engine.h"
 #include "xpose.h"
