@@ -1798,7 +1798,7 @@ int epic_run(epic_plan_t plan, const void* const* efield, int64_t n_samples, dou
   const bool batched = !any_band && all_batchable && (plan->batch == 1 || (plan->batch == 0 && na_arr > 1));
   // a graph needs the batched form or a fused run; a single array of float samples
   // at 64 x 64 and above asks for EPIC_OPT_BATCH = 1 as well, as it did when it had
-  // no engine in the persistent kernels (callers rely on the error)
+  // no engine in the persistent kernels: what was refused stays so
   bool graph_fused = fused;
   for (const ArrayPlan& ap : plan->arrays) graph_fused = graph_fused && !(ap.h.efmt == EPIC_CF32 && ap.h.nx >= 64);
   if (plan->graph && !batched && !graph_fused)
