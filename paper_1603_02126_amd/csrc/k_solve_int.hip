@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kSolveMainThreads) void k_solve_int(SolveArgs a) {
 // at least one 16-byte piece, a chunk's rows within 32-bit offsets: the
 // matrix-core solve.  Its steps per interval cost the same few microseconds
 // however short the interval: 256 antennas of ci4, us per interval, FP64 FMAs
-// against it, 2.4 / 3.2 at 8 samples, 3.5 / 3.3 at 25, 7.6 / 4.4 at 100.
+// against it, 2.4 / 3.3 at 8 samples, 3.5 / 3.6 at 25, 7.6 / 4.6 at 100.
 bool solve_by_int(const SolveArgs& a) {
   const int64_t RB = int64_t(a.Na) * efmt_bytes(a.fmt);
   return std::min(a.t_cal, a.n_t) >= kSolveIntMinSamples && a.fmt != kCF32 && a.Na <= kSolveIntMaxAnt && RB >= 16 &&

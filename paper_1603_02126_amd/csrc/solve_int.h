@@ -15,23 +15,27 @@
 //                columns = 16 bytes (two antennas in four lanes' columns).
 // The digit sums are exact in int32 and meet in FP64 at the end, so a sum is
 // rounded once where an FP64 sum rounds at every term.  Its factors are rounded
-// to 2^-61 of the largest of them, which keeps 53 bits of each while the c of
-// the antennas lie within 2^8 of each other (kDigitSpan).  They need not: an
-// antenna without a signal (K = Q = 0, g' = gamma g) has a c that grows by
-// 1 / gamma per interval, multiplies zeros only, and would take every digit from
-// the others' coefficients.  An interval whose c spread wider, and all after it,
-// go to the FP64 solve (solve_channel_fmt), which rounds each term by itself: 128
-// channels, 100 intervals of 100 samples, 256 antennas ci4, 439 us, with one
-// silent antenna 767 (in FP64 throughout 755).
+// to 2^-61 of the largest of them.  That is no less than FP64 keeps of a sum in
+// which the largest takes part, but an antenna without a signal multiplies zeros
+// only, while its c grows by 1 / gamma per interval (K = Q = 0, g' = gamma g) and
+// would take every digit from the others' coefficients.  So an antenna whose
+// samples of the last interval were all zero is left out (its term is zero), and if
+// it has a sample after all, the interval is done again in FP64
+// (solve_channel_fmt), as are all after it; likewise where the c of the antennas
+// with a signal spread by more than 2^12 (kDigitSpan; a cold start of the HERA
+// shape passes through 2^11), which bounds what an antenna that falls silent takes
+// from the others in that interval.  (Keeping to 2^8 with all antennas in the scale
+// sent a few channels of that start to FP64, its solve 0.31 -> 0.53 ms, and every
+// run with a silent antenna, 100 intervals of 256 antennas ci4 450 -> 767 us.)
 //   What remains per interval is latency: five barriers, the digits and the
 // update.
 // Largest error of P over the largest |P| against exact sums: 16 antennas 6.5e-17
 // (FP64 sums 1.5e-16), 256 6.6e-17 (3.3e-16), 900 8.6e-17 (4.6e-16).
 // 64 channels, 50 intervals, per interval, FP64 FMAs (four per sample in each
 // contraction, after two conversions) against this:
-//   intervals of 100: 256 antennas ci4 7.6 -> 4.4 us, 255 ci8 (rows of no
-//   alignment) 28.5 -> 4.8, 350 ci8 19.1 -> 7.4, 900 ci8 51 -> 26;
-//   of 25: 3.5 -> 3.3, 9.1 -> 3.9, 6.8 -> 4.0, 14.0 -> 7.6.
+//   intervals of 100: 256 antennas ci4 7.6 -> 4.6 us, 255 ci8 (rows of no
+//   alignment) 28.5 -> 5.0, 350 ci8 19.1 -> 7.6, 900 ci8 51 -> 26;
+//   of 25: 3.5 -> 3.6, 9.1 -> 4.1, 6.8 -> 4.2, 13.9 -> 7.7.
 #pragma once
 #include "solve.h"
 
@@ -44,8 +48,8 @@ constexpr int kSolveIntMaxAnt = 1024;
 constexpr int64_t kSolveIntMinSamples = 20;   // of an interval
 constexpr int kSolveIntRows = 128;          // samples of a chunk at most
 constexpr int kRowBytes = 80;                // a block's row in the LDS: 64 bytes, padded
-constexpr int kDigitSpan = 8;                // exponents of the c of an interval
-constexpr uint32_t kWide = 0xffffffffu;      // in place of the largest |P| (abs_hi): the c spread wider
+constexpr int kDigitSpan = 12;               // exponents of the c of an interval
+constexpr uint32_t kStop = 0xffffffffu;      // in place of the largest |c| or |P| (abs_hi): not by this solve
 constexpr int kDigitBlock = 16 * 16 + 16;   // bytes: 16 digit rows x 16 contraction entries, padded
 
 struct SolveIntSmem {
@@ -99,8 +103,8 @@ __device__ __forceinline__ double digit_sum(ivec4 d) {
   return fma(fma(fma(double(d[3]), 256.0, double(d[2])), 256.0, double(d[1])), 256.0, double(d[0]));
 }
 
-// Returns the number of intervals solved: n_int, or fewer where the next one's
-// c spread too wide (the gains are then those at its start; its u is written).
+// Returns the number of intervals solved: n_int, or fewer where the next one is
+// left to the FP64 solve (the gains are then those at its start; its u is written).
 template <int FMT, int J, bool PUBLISH>
 __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint8_t* smem, int* progress = nullptr) {
   static_assert(FMT == kCI4 || FMT == kCI8, "integer samples");
@@ -191,18 +195,21 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
   };
 
   double2 g[J], A[J], invD[J];
+  double2 At[J];                    // A in the tap: zero for silent antennas
   uint8_t hold[J];
-  uint32_t st[J];
+  uint32_t st[J], st_was[J];
+  uint32_t heard[J];                // the last interval's samples: 0 if all were zero
   static_for<0, J>([&](auto jc) {
     constexpr int j = decltype(jc)::value;
     const int an = tid + T * j;
-    g[j] = A[j] = invD[j] = make_double2(0.0, 0.0);
+    g[j] = A[j] = At[j] = invD[j] = make_double2(0.0, 0.0);
     hold[j] = 0;
-    st[j] = 0u;
+    st[j] = st_was[j] = 0u;
+    heard[j] = 1u;
     if (an < Na) {
       const int64_t ia = int64_t(f) * Na + an;
       g[j] = gload(a.gains + ia);
-      A[j] = gload(a.A + ia);
+      At[j] = A[j] = gload(a.A + ia);
       const double2 D = gload(a.D + ia);
       const double d2 = D.x * D.x + D.y * D.y;
       invD[j] = make_double2(a.na_eff * D.x / d2, -a.na_eff * D.y / d2);
@@ -231,23 +238,26 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
   store(t, nr);
   double rr[J];
   uint32_t hc = 0u;
+  uint32_t redo = 0u;                    // kStop: an antenna left out of the last interval had a signal
+  bool undo = false;
   // one loop over the chunks of all intervals: with a loop over an interval's
   // chunks inside, what the requests compute was hoisted to its front and ran
   // for every interval in the recurrence's way
   while (true) {
     const bool more = n + 1 < a.n_int, ends = i + 1 == (more ? full : last).nch;
-    uint32_t mp = 0u;                          // largest |P|, or kWide
+    uint32_t mp = 0u;                          // largest |P|, or kStop
     if (i == 0) {
     // c_a = A_a u_a / Na = A_a conj(g_a) r_a, u_a = 1 / g_a (zero for flagged antennas)
     double2 c[J];
-    uint32_t mx = 0u;
+    uint32_t m[J], mx = redo;
     static_for<0, J>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
       const int an = tid + T * j;
       rr[j] = recip_nr(a.na_eff * (g[j].x * g[j].x + g[j].y * g[j].y));
-      c[j] = zmul(A[j], make_double2(g[j].x * rr[j], -g[j].y * rr[j]));
+      c[j] = zmul(At[j], make_double2(g[j].x * rr[j], -g[j].y * rr[j]));
       if (an >= Na || (hold[j] & kHoldFlagged)) c[j] = make_double2(0.0, 0.0);
-      mx = max(mx, max(abs_hi(c[j].x), abs_hi(c[j].y)));
+      m[j] = max(abs_hi(c[j].x), abs_hi(c[j].y));
+      mx = max(mx, m[j]);
       if (an < Na) {
         const double s = a.na_eff * rr[j];   // 1 / |g|^2
         const float2 uf = hold[j] & kHoldFlagged ? make_float2(0.0f, 0.0f) : make_float2(float(g[j].x * s), float(-g[j].y * s));
@@ -263,12 +273,13 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
     if (lane == 63) mx_c[wave] = mx;
     if constexpr (PUBLISH) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's u stores are done
     __syncthreads();
+    hc = max8(mx_c);
+    mp = hc == kStop ? kStop : 0u;             // (left below, with the other reason to stop)
     if constexpr (PUBLISH) {
-      if (tid == 0)
+      if (tid == 0 && hc != kStop)
         __hip_atomic_store((__attribute__((address_space(1))) int*)(progress + f), n + 1, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
-    hc = max8(mx_c);
     const bool finite = hc < 0x7ff00000u;      // uniform
     const int sc = digit_scale(hc);
     // a magnitude from 1 to `below` lies under the span
@@ -277,7 +288,7 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
       constexpr int j = decltype(jc)::value;
       const int an = tid + T * j;
       if (an < Na) {
-        if (max(abs_hi(c[j].x), abs_hi(c[j].y)) - 1u < below) mp = kWide;
+        if (m[j] - 1u < below) mp = kStop;
         const double x = finite ? c[j].x : 0.0, y = finite ? c[j].y : 0.0;
         const long long iy = fixed_point(y, sc);
         const unsigned long long dx = digits(fixed_point(x, sc)), dy = digits(iy), dn = digits(-iy);
@@ -331,7 +342,10 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
       if (lane == 63) mx_p[wave] = mp;
       __syncthreads();
       const uint32_t hp = max8(mx_p);
-      if (hp == kWide) break;                  // uniform
+      if (hp == kStop) {                       // uniform
+        undo = hc == kStop;
+        break;
+      }
       const bool pfinite = hp < 0x7ff00000u;
       const int sp = digit_scale(hp);
       {
@@ -431,7 +445,13 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
       const int an = tid + T * j;
       if (an < Na) {
         const double2 k = K_l[an];
-        g[j] = epical_step_r(make_double2(k.x * inv_n, k.y * inv_n), Q_l[an] * inv_n, A[j], invD[j], g[j], rr[j], hold[j],
+        const double q = Q_l[an];
+        const uint32_t now = abs_hi(q);
+        if (heard[j] == 0u && now) redo = kStop;
+        heard[j] = now;
+        At[j] = now ? A[j] : make_double2(0.0, 0.0);
+        st_was[j] = st[j];
+        g[j] = epical_step_r(make_double2(k.x * inv_n, k.y * inv_n), q * inv_n, A[j], invD[j], g[j], rr[j], hold[j],
                              a.gamma, &st[j]);
         gstore(a.g_hist + (int64_t(n + 1) * a.F + f) * Na + an, g[j]);
       }
@@ -443,10 +463,21 @@ __device__ __forceinline__ int solve_channel_int(const SolveArgs& a, int f, uint
     t += nr;
     nr = nr_next;
   }
+  if (n == a.n_int) {
+    const bool any = __any(redo != 0u);
+    if (lane == 63) mx_c[wave] = any;
+    __syncthreads();
+    undo = max8(mx_c) != 0u;
+  }
+  if (undo) --n;                         // the last update is void
   static_for<0, J>([&](auto jc) {
     constexpr int j = decltype(jc)::value;
     const int an = tid + T * j;
     if (an < Na) {
+      if (undo) {
+        g[j] = gload(a.g_hist + (int64_t(n) * a.F + f) * Na + an);
+        st[j] = st_was[j];
+      }
       gstore(a.gains + int64_t(f) * Na + an, g[j]);
       if (a.status) {
         uint32_t* sp = a.status + int64_t(f) * Na + an;

@@ -113,3 +113,27 @@ def test_silent_antenna_in_launches_of_one_array(cuda, na, efmt):
             torch.cuda.synchronize()
             assert gain_err(g.cpu().numpy(), ref["gains"][-1]) <= GAIN_RTOL
             assert image_err(imgs[0].cpu().numpy(), ref["image"]).max() <= IMAGE_RTOL
+
+
+@pytest.mark.parametrize("overlap", [0, 1])
+@pytest.mark.parametrize("na,efmt,t_cal,pattern", [
+    (48, synth.FMT_CI8, 20, "1110001000000111"),    # falls silent and comes back, twice
+    (33, synth.FMT_CI4, 150, "100000001"),          # in the last interval, several chunks each
+    (700, synth.FMT_CI8, 30, "0000100"),            # silent from the first interval on
+])
+def test_antenna_comes_and_goes(cuda, overlap, na, efmt, t_cal, pattern):
+    """An antenna with a signal in the intervals marked 1 only; where it comes
+    back, in the interval's last sample alone."""
+    n_int = len(pattern)
+    wl = synth.config_small(n=32 if na <= 256 else 128, efmt=efmt, n_ant=na, n_chan=1 if na > 256 else 2,
+                            n_samples=n_int * t_cal, t_cal=t_cal, gamma=0.2)
+    packed = synth.make_efield(wl)
+    for n, on in enumerate(pattern):
+        t = slice(n * t_cal, (n + 1) * t_cal)
+        if on == "0":
+            packed[t, :, 5] = 0
+        elif n and pattern[n - 1] == "0":
+            packed[n * t_cal:(n + 1) * t_cal - 1, :, 5] = 0
+    ref = oracle_run(wl, packed)
+    hist, _ = _run(wl, packed, cuda, overlap)
+    assert gain_err(hist, ref["gains"]) <= GAIN_RTOL
