@@ -335,17 +335,21 @@ __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, 
   float2 v[N];
   Raw raw[APL];
   constexpr int bpe = FMT == kCF32 ? 8 : FMT == kCI8 ? 2 : 1;
-  auto fetch_raw = [&](const SnapCursor& c, const SnapCursor& last) {
-    const int64_t t = c.valid() ? c.t() : last.t();
-    const uint8_t* row = a.efield + (t * a.F + f) * int64_t(a.Na) * bpe;
+  // (the condition keeps these loads ahead of the column FFT, where the compiler
+  // otherwise moves them behind it, against the image stores that they then wait
+  // with: 256 antennas ci4, 128 channels x 10000, an image every sample, 6.5 ms
+  // without it, 5.9 with; every 100 samples 4.68, 4.58)
+  auto fetch_raw = [&](const SnapCursor& c) {
+    const uint8_t* row = a.efield + (c.t() * a.F + f) * int64_t(a.Na) * bpe;
     static_for<0, APL>([&](auto ic) {
-      raw[decltype(ic)::value] = load_raw_global(row, min(lam + N * decltype(ic)::value, a.Na - 1), FMT);
+      const int an = lam + N * decltype(ic)::value;
+      raw[decltype(ic)::value] = c.valid() && an < a.Na ? load_raw_global(row, an, FMT) : Raw{0u, 0u};
     });
   };
   // the waves are independent: each walks its own windows
   SnapCursor cur{wb + wave, 0, we, INFLIGHT, a.t_acc, a.n_t};
   IntervalCursor interval(a.t_cal);
-  if (cur.valid()) fetch_raw(cur, cur);
+  fetch_raw(cur);
   while (cur.valid()) {
     __builtin_amdgcn_s_setprio(1);
     const float2* urow = a.u + (interval.at(cur.t()) * a.F + f) * int64_t(a.Na);
@@ -372,7 +376,7 @@ __device__ __forceinline__ void image_item_pair_snap(const ImageArgs& a, int f, 
     fft_reg<N, +1>(v);
     SnapCursor nxt = cur;
     nxt.next();
-    fetch_raw(nxt, cur);
+    fetch_raw(nxt);
     add_norms<N>(acc, v);
     if (cur.last()) snap_store<N>(a, f, cur.j, acc, lam);
     cur = nxt;
