@@ -53,10 +53,10 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC_SOURCES = ("k_image.hip", "image_fft.h", "image_cls.h", "engine.h", "fft_reg.h", "xpose.h", "epic_internal.h",
                    "epic_api.hip", "splits.h")
 TRAFFIC_MEASURED = {
-    "lwa": {"sources_sha256": "2eed0b3419fffb730fe00e12a0d64eaa126ae41e15e5f36ddfc296204d9416e4",
-            "fetch_kib": 173354.0, "fetch_scale": 2.000, "write_kib": 12288.0, "write_scale": 1.000},
-    "lwa_snapshot1": {"sources_sha256": "cf146e0725967256acff341d28546c9dbb3940fe1e8653b838f13ed1e69d1254",
-                      "fetch_kib": 174325.0, "fetch_scale": 2.000, "write_kib": 20480115.3, "write_scale": 1.000},
+    "lwa": {"sources_sha256": "73202053ebab7be8552e9c329fe9dcad567f761441857346ecb1b0f73ed2ef92",
+            "fetch_kib": 173359.0, "fetch_scale": 2.000, "write_kib": 12288.0, "write_scale": 1.000},
+    "lwa_snapshot1": {"sources_sha256": "73202053ebab7be8552e9c329fe9dcad567f761441857346ecb1b0f73ed2ef92",
+                      "fetch_kib": 173074.1, "fetch_scale": 2.000, "write_kib": 20480082.1, "write_scale": 1.000},
 }
 
 
@@ -66,7 +66,7 @@ TRAFFIC_MEASURED = {
 # wave, two waves per SIMD, four cycles per instruction and wave) and the
 # fraction of the launch the LDS is busy (SQ_LDS_IDX_ACTIVE per CU).
 SQ_MEASURED = {
-    "lwa": {"sources_sha256": "2eed0b3419fffb730fe00e12a0d64eaa126ae41e15e5f36ddfc296204d9416e4", "valu_issue_frac": 0.57, "lds_busy_frac": 0.57},
+    "lwa": {"sources_sha256": "73202053ebab7be8552e9c329fe9dcad567f761441857346ecb1b0f73ed2ef92", "valu_issue_frac": 0.57, "lds_busy_frac": 0.57},
 }
 
 
